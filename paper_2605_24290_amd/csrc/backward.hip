@@ -58,7 +58,7 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
     const float2 *__restrict__ rad, const int4 *__restrict__ chunks, int split, int64_t Kp, DevGrid g,
     int tx_mode, const float *__restrict__ C, const float *__restrict__ dC, const float *__restrict__ dP,
     const float *__restrict__ dA, const float *__restrict__ Tfin, const int *__restrict__ nlast, float *__restrict__ dS,
-    float *__restrict__ g2d, uint8_t *__restrict__ live, DetPartials det)
+    float *__restrict__ g2d, uint8_t *__restrict__ live, DetPartials det, const int4 *__restrict__ vinfo)
 {
     constexpr int NV = 6 + 2 * R;   // values per entry: six record gradients, then (Re, Im) per receiver
     __shared__ BlendStage st;
@@ -74,6 +74,7 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
     const int view = ch.x, j0 = ch.y + sub * R, nrx = min(ch.z - sub * R, R);
     if (nrx <= 0) return;   // uniform over the block, before any barrier
     const int tread = tx_mode ? view : j0;
+    const int4 vr = vinfo[view];   // its first row and rows
     const int ty = tile / g.tiles_x, tx = tile - ty * g.tiles_x;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int row = ty * TILE + 8 * (wv >> 1) + (lane >> 3), col = tx * TILE + 8 * (wv & 1) + (lane & 7);
@@ -138,9 +139,14 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
             const int64_t s = max((int64_t)p - (int64_t)view * Kp, (int64_t)0);
 #pragma unroll
             for (int r = 0; r < R; r++)
-                s_rad[r][t] = (r < nrx) ? rad[(size_t)(j0 + r) * Kp + s] : make_float2(0.f, 0.f);
+                s_rad[r][t] = (r < nrx) ? rad[rad_index(vr, Kp, s, j0 + r)] : make_float2(0.f, 0.f);
         }
-        stage_batch(st, srec, p, t < cnt, tx, ty, g);
+        float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;
+        if (t < cnt) {
+            q0 = srec[2 * (size_t)p];
+            q1 = srec[2 * (size_t)p + 1];
+        }
+        stage_batch(st, q0, q1, p, t < cnt, tx, ty, g);
         const int n = st.len[wv];
         for (int i = n - 1; i >= 0; i--) {
             const int e = st.list[wv][i];
@@ -1354,7 +1360,7 @@ static hipError_t blend_bwd_launch(Workspace &ws, const float *C, const float *d
                        ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.rad.as<float2>(),
                        ws.d_chunks, split, ws.Kp, ws.g, ws.mode == RXGS_MODE_TX ? 1 : 0, C, dC, dP, dA,
                        ws.Tfin.as<float>(), ws.nlast.as<int>(), ws.dS.as<float>(), ws.g2d.as<float>(),
-                       ws.live.as<uint8_t>(), det);
+                       ws.live.as<uint8_t>(), det, ws.d_vinfo);
     return hipGetLastError();
 }
 

@@ -30,6 +30,15 @@ __device__ __forceinline__ uint64_t match_key8(uint32_t d, uint64_t m)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Element of (row j, sorted position s) in the radiance buffer: a view's rows
+// lie together in one block, position by position (vi: the view's first row
+// and rows), so that the multi-receiver blend and its backward read the rows
+// of an entry as one run; a view of one row is a plain row of Kp elements.
+__device__ __forceinline__ size_t rad_index(const int4 &vi, int64_t Kp, int64_t s, int64_t j)
+{
+    return (size_t)vi.x * (size_t)Kp + (size_t)s * (size_t)vi.y + (size_t)(j - vi.x);
+}
+
 // Blend exponent of one (pixel, record): log2 of o exp(-q/2), with the record
 // holding (-a/2, -b, -c/2) log2(e) and log2(o).  Written with explicit fmaf so
 // that the forward and the backward evaluate bit-identical weights.
@@ -181,16 +190,14 @@ __device__ __forceinline__ int subtile_mask(const float4 &r0, const float4 &r1, 
     return m;
 }
 
-// Stage the batch entry of this thread (if `has`) and build the per-wave lists.
-// All threads of the block must call it.
-__device__ __forceinline__ void stage_batch(BlendStage &st, const float4 *__restrict__ srec, uint32_t p, bool has,
+// Stage the batch entry of this thread (if `has`: position p, record r0, r1)
+// and build the per-wave lists.  All threads of the block must call it.
+__device__ __forceinline__ void stage_batch(BlendStage &st, float4 r0, const float4 r1, uint32_t p, bool has,
                                             int tx, int ty, const DevGrid &g, bool nearp = true)
 {
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     int m = 0;
     if (has) {
-        float4 r0 = srec[2 * (size_t)p];
-        const float4 r1 = srec[2 * (size_t)p + 1];
         const float Wf = (float)g.W, halfW = 0.5f * (float)g.W;
         const float tcol = (float)(tx * TILE) + 7.5f;
         // representative of the azimuth closest to this tile's centre

@@ -1072,13 +1072,17 @@ __global__ __launch_bounds__(BLOCK) void k_ranges(const uint32_t *__restrict__ s
 __global__ __launch_bounds__(BLOCK) void k_rad_direct(const float2 *__restrict__ radiance,
                                                       const uint32_t *__restrict__ order,
                                                       const unsigned long long *__restrict__ counters,
-                                                      const int *__restrict__ rxview, int N, int64_t Kp,
+                                                      const int *__restrict__ rxview,
+                                                      const int4 *__restrict__ vinfo, int N, int64_t Kp,
                                                       int64_t K, float2 *__restrict__ rad)
 {
     const int64_t idx = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (idx >= (int64_t)N * Kp) return;
-    const int64_t j = idx / Kp, s = idx - j * Kp;
-    const int v = rxview[j];
+    // (the view of row idx / Kp owns the element, whatever the row: a view's
+    // rows share their block of the buffer)
+    const int v = rxview[idx / Kp];
+    const int4 vi = vinfo[v];
+    const int64_t s = (idx - (int64_t)vi.x * Kp) / vi.y;
     if (s < (int64_t)counters[2 * (size_t)v]) rad[idx] = radiance[min((int64_t)order[(size_t)v * Kp + s], K - 1)];
 }
 
@@ -1243,6 +1247,14 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_local(const float *__restrict__ W
     block_absmax_to(m, amax);
 }
 
+// one row of the radiance buffer (exports)
+__global__ __launch_bounds__(BLOCK) void k_rad_row(const float2 *__restrict__ rad, int4 vi, int64_t Kp, int j,
+                                                   float2 *__restrict__ out)
+{
+    const int64_t s = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+    if (s < Kp) out[s] = rad[rad_index(vi, Kp, s, j)];
+}
+
 // Per-(receiver, Gaussian) layers 2 and 3 on FP32 MFMA (v_mfma_f32_32x32x2f32).
 // One wave per work item = (view, 32 consecutive sorted positions, up to 16
 // receivers of that view).  The wave computes H2^T = W2 X1^T for its 32
@@ -1257,7 +1269,8 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_pairs_f32(const float *__restrict
                                                      const uint32_t *__restrict__ order,
                                                      const int4 *__restrict__ items, int nitems, int64_t Kp,
                                                      int64_t K, const unsigned long long *__restrict__ counters,
-                                                     float2 *__restrict__ rad, const int *__restrict__ nlive)
+                                                     float2 *__restrict__ rad, const int *__restrict__ nlive,
+                                                     const int4 *__restrict__ vinfo)
 {
     if (nlive) nitems = min(nitems, *nlive);
     __shared__ float s_w2a[2 * 32 * 64];
@@ -1325,7 +1338,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_pairs_f32(const float *__restrict
         }
         o0 += __shfl_xor(o0, 32);
         o1 += __shfl_xor(o1, 32);
-        if (h == 0 && valid) rad[(size_t)j * Kp + s] = make_float2(o0 + b30, o1 + b31);
+        if (h == 0 && valid) rad[rad_index(vinfo[view], Kp, s, j)] = make_float2(o0 + b30, o1 + b31);
     }
     }
 }
@@ -1448,7 +1461,8 @@ __device__ __forceinline__ void mlp_pairs_walk(const float *__restrict__ Lp, con
                                                const float4 *s_b2, const float4 *s_w3, const half8 *s_w1h,
                                                const float4 *s_b1, float l1unscale, float b30, float b31, float sx,
                                                const uint32_t *__restrict__ order, const int4 *__restrict__ items,
-                                               int nitems, int64_t Kp, int64_t K, float2 *__restrict__ rad)
+                                               int nitems, int64_t Kp, int64_t K, float2 *__restrict__ rad,
+                                               const int4 *__restrict__ vinfo)
 {
     const int lane = threadIdx.x & 63, h = lane >> 5, pl = lane & 31;
     const float isx = 1.f / sx;
@@ -1489,7 +1503,7 @@ __device__ __forceinline__ void mlp_pairs_walk(const float *__restrict__ Lp, con
         }
         const int nj = dc.w & 255;
         const bool valid = pl < (dc.w >> 8);
-        const int64_t s = dc.y + pl;
+        const size_t rbase = rad_index(vinfo[dc.x], Kp, dc.y + pl, dc.z);
         const bool more = n + 1 < nmine;
         for (int jj = 0; jj < nj; jj++) {
             int z0 = 0;
@@ -1571,7 +1585,7 @@ __device__ __forceinline__ void mlp_pairs_walk(const float *__restrict__ Lp, con
                 o0 *= isx;
                 o1 *= isx;
             }
-            if (h == 0 && valid) rad[(size_t)(dc.z + jj) * Kp + s] = make_float2(o0 + b30, o1 + b31);
+            if (h == 0 && valid) rad[rbase + jj] = make_float2(o0 + b30, o1 + b31);
         }
         dc = dn;
         dn = dnn;
@@ -1592,7 +1606,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) v
                                                      const uint32_t *__restrict__ order,
                                                      const int4 *__restrict__ items, int nitems, int64_t Kp,
                                                      int64_t K, const unsigned *__restrict__ amax,
-                                                     float2 *__restrict__ rad, const int *__restrict__ nlive)
+                                                     float2 *__restrict__ rad, const int *__restrict__ nlive,
+                                                     const int4 *__restrict__ vinfo)
 {
     if (nlive) nitems = min(nitems, *nlive);
     __shared__ half8 s_w1h[FUSED ? 8 * 64 : 1];
@@ -1629,13 +1644,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) v
     const float bound = __uint_as_float(mg) + (FUSED ? lbound : __uint_as_float(ml));
     if (bound < 32768.f) {
         mlp_pairs_walk<false, FUSED>(Lp, feat, Gp, s_w2h, s_b2, s_w3, s_w1h, s_b1, l1unscale, b30, b31, 1.f, order,
-                                     items, nitems, Kp, K, rad);
+                                     items, nitems, Kp, K, rad, vinfo);
     } else {
         int e = 0;
         frexpf(bound, &e);   // bound < 2^e
         const float sx = (e > 15 && e < 128) ? ldexpf(1.f, 15 - e) : 1.f;
         mlp_pairs_walk<true, FUSED>(Lp, feat, Gp, s_w2h, s_b2, s_w3, s_w1h, s_b1, l1unscale, b30, b31, sx, order,
-                                    items, nitems, Kp, K, rad);
+                                    items, nitems, Kp, K, rad, vinfo);
     }
 }
 
@@ -2051,63 +2066,209 @@ __global__ __launch_bounds__(BLEND1_THREADS) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-// Several receivers per workgroup: entries staged once per batch (record,
-// batch index lists per wave), radiance of the R receivers in LDS.  One wave's
-// walk over its staged list, free of branches per entry: an entry
-// below the alpha threshold, or met after the lane terminated, gets weight 0,
-// which leaves T and the sums bit-identical to skipping it.  WRAP: some entry of
-// the list spans more than half the azimuth circle, so pixel offsets are
-// wrapped into [-W/2, W/2) (selects).  SAVE: track the stop index and the
-// composited count (saved states and statistics only).  MARK: flag in s_mark
-// every entry that some lane composites (the weights-only pass).
-template <int R, bool SAVE, bool WRAP, bool MARK = false, bool DETECT = false>
-__device__ __forceinline__ void blend_walk_multi(const BlendStage &st, const float2 (*s_rad)[BLOCK], int wv, int n,
-                                           int lbase, float colf, float rowf, float Wf, float halfW, float &T,
-                                           float2 (&acc)[R], int &last, uint32_t &ncomp, uint32_t &neval,
-                                           uint32_t &nslot, bool &done, unsigned char *s_mark = nullptr,
-                                           int i_begin = 0, uint2 *myrec = nullptr, int *fcount = nullptr,
-                                           uint8_t *mark = nullptr)
+// Several receivers (rows) per workgroup: entries staged once per batch
+// (record, batch index lists per wave) and one wave's walk over its list.  The
+// compositing sums are a contraction over the entries, C[row, pixel] =
+// sum_e s[row, e] (T w)[e, pixel], and run on the matrix cores: per two
+// entries, v_mfma_f32_32x32x2_f32 with A = the entries' radiance (32 rows: Re
+// and Im of 16 receivers) and B = their weights for 32 of the wave's 64 pixels
+// (the two entries' weight registers, one pixel per lane, swapped into B's
+// layout by one v_permlane32_swap).  The instruction adds its two products one
+// after the other, each with one rounding, so the sums are bit for bit those
+// of an FMA per entry in list order.  A's elements are read where they are
+// used, a group of four entries ahead: the rows of a position lie together in
+// the radiance buffer, so a lane half reads one entry's 32 values as one run.
+// The vector ALU keeps the weights (about 19 instructions an entry), four
+// entries at a time so that their LDS reads and exponentials overlap; only
+// the transmittance is a serial chain.  The kernel is bound by the vector ALU
+// (0.83 of its cycles on the coverage map).  Before, every entry cost 2 FMAs
+// and a broadcast LDS read per receiver: 64 receivers of one transmitter (50k
+// Gaussians) 66 -> 35 us, 16 transmitters with 700 receivers (200k) 433 ->
+// 207 us, the 4,096-receiver coverage map (1M) 1427 -> 600 us.
+template <int NB>
+struct BlendRad {
+    float a[2][NB > 0 ? NB : 1];   // per pair of entries and 16 receivers: the lane's A element
+};
+
+// the radiance elements of the four entries from list index i0 (0 where the
+// stage has none for an entry)
+template <int NB>
+__device__ __forceinline__ BlendRad<NB> blend_rad4(const BlendStage &st, const uint2 *s_roff, const float *rad_v,
+                                                   const int (&rl)[NB > 0 ? NB : 1], int wv, int i0, int n)
 {
-    for (int i = i_begin; i < n; i++) {
-        if (SAVE) {
-            neval += done ? 0u : 1u;
-            nslot++;
-        }
-        const int e = st.list[wv][i];
-        const float4 r0 = st.r0[e];
-        const float4 r1 = st.r1[e];
-        float du = (colf - r0.x) - r0.y;
-        if (WRAP) {
-            du = du >= halfW ? du - Wf : du;
-            du = du < -halfW ? du + Wf : du;
-        }
-        const float dv = (rowf - r0.z) - r0.w;
-        float w = fminf(W_MAX, __builtin_amdgcn_exp2f(blend_exponent(du, dv, r1)));
-        const bool inc = !done && w >= ALPHA_MIN;
-        w = inc ? w : 0.f;
-        const float tw = T * w;
+    BlendRad<NB> v;
+    const int h = (threadIdx.x & 63) >> 5;
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            const float2 sv = s_rad[r][e];
-            acc[r].x = fmaf(tw, sv.x, acc[r].x);
-            acc[r].y = fmaf(tw, sv.y, acc[r].y);
+    for (int k = 0; k < 2; k++) {
+        const int i = min(i0 + 2 * k + h, n - 1);
+        const uint2 o = s_roff[st.list[wv][i]];
+        const float *src = rad_v + (((size_t)(o.y & 0x7FFFFFFFu) << 32) | o.x);
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            const float x = src[rl[b]];
+            v.a[k][b] = (int)o.y < 0 ? 0.f : x;
         }
-        T = T * (1.f - w);
-        if (SAVE) {
-            last = inc ? lbase + e : last;
-            ncomp += inc ? 1u : 0u;
-        }
-        if (MARK && inc) s_mark[e] = 1;
-        if (DETECT && inc) {
-            if (*fcount < FAR_REC && myrec) {
-                myrec[*fcount] = make_uint2(__float_as_uint(tw), st.p[e]);
-                mark[st.p[e] / MLP_PAIRS] = 1;
-            }
-            ++*fcount;
-        }
-        done = done || T < T_EPS;
-        if ((i & 3) == 3 && __all(done)) break;
     }
+    return v;
+}
+
+// One wave's walk over its staged list, four entries at a time (the last
+// group is filled with its own first entry at weight 0), free of branches per
+// entry: an entry below the alpha threshold, or met after the lane terminated,
+// gets weight 0, which leaves T and the sums bit-identical to skipping it.
+// wrap: some entry of the list spans more than half the azimuth circle, so
+// pixel offsets are wrapped into [-W/2, W/2) (selects).  SAVE: track the stop
+// index and the composited count (saved states and statistics only).  MARK:
+// flag in s_mark every entry that some lane composites (the weights-only
+// pass).  Entries at index i_far and later lie past the position prefix: those
+// a lane composites are recorded (FarState).  (A composited entry's T w is
+// positive: T >= 1e-4 and w >= 1/255.)
+template <int NB, bool SAVE, bool MARK>
+__device__ __forceinline__ void blend_walk_mm(const BlendStage &st, const uint2 *s_roff, const float *rad_v,
+                                              const int (&rl)[NB > 0 ? NB : 1], int wv, int i_far, int n,
+                                              int lbase, bool wrap, float colf, float rowf, float Wf, float halfW,
+                                              float &T, floatx16 (&acc)[NB > 0 ? NB : 1][2], int &last,
+                                              uint32_t &ncomp, uint32_t &neval, uint32_t &nslot, bool &done,
+                                              unsigned char *s_mark, uint2 *myrec, int &fcount, uint8_t *mark)
+{
+    if (n <= 0) return;
+    BlendRad<NB> ra;
+    if constexpr (NB > 0) ra = blend_rad4<NB>(st, s_roff, rad_v, rl, wv, 0, n);
+    // (one exit, at the end: the loop then has one set of accumulators)
+    int i0 = 0;
+    do {
+        const ushort4 l4 = *reinterpret_cast<const ushort4 *>(&st.list[wv][i0]);
+        const int e[4] = {l4.x, i0 + 1 < n ? l4.y : l4.x, i0 + 2 < n ? l4.z : l4.x, i0 + 3 < n ? l4.w : l4.x};
+        float4 r0[4], r1[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            r0[k] = st.r0[e[k]];
+            r1[k] = st.r1[e[k]];
+        }
+        // the next group's radiance, a group ahead
+        BlendRad<NB> rn;
+        if constexpr (NB > 0) rn = blend_rad4<NB>(st, s_roff, rad_v, rl, wv, min(i0 + 4, n - 1), n);
+        // (all reads of the group in flight together)
+        __builtin_amdgcn_sched_barrier(0);
+        float du[4], w[4], tw[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) du[k] = (colf - r0[k].x) - r0[k].y;
+        if (wrap) {   // uniform
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                du[k] = du[k] >= halfW ? du[k] - Wf : du[k];
+                du[k] = du[k] < -halfW ? du[k] + Wf : du[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const float dv = (rowf - r0[k].z) - r0[k].w;
+            const float wr = fminf(W_MAX, __builtin_amdgcn_exp2f(blend_exponent(du[k], dv, r1[k])));
+            w[k] = i0 + k < n && wr >= ALPHA_MIN ? wr : 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            if (SAVE) {
+                const bool real = i0 + k < n;   // uniform
+                neval += (real && !done) ? 1u : 0u;
+                nslot += real ? 1u : 0u;
+            }
+            const float wk = done ? 0.f : w[k];
+            tw[k] = T * wk;
+            T = T * (1.f - wk);
+            if (SAVE) {
+                last = wk > 0.f ? lbase + e[k] : last;
+                ncomp += wk > 0.f ? 1u : 0u;
+            }
+            if (MARK && wk > 0.f) s_mark[e[k]] = 1;
+            done = done || T < T_EPS;
+        }
+        if (!MARK && i0 + 4 > i_far) {   // uniform
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                if (i0 + k >= i_far && tw[k] > 0.f) {
+                    if (fcount < FAR_REC && myrec) {
+                        const uint32_t pe = st.p[e[k]];
+                        myrec[fcount] = make_uint2(__float_as_uint(tw[k]), pe);
+                        mark[pe / MLP_PAIRS] = 1;
+                    }
+                    ++fcount;
+                }
+        }
+        if constexpr (NB > 0) {
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tw[2 * k]),
+                                                                 __float_as_uint(tw[2 * k + 1]), false, false);
+                const float b0 = __uint_as_float(sw[0]), b1 = __uint_as_float(sw[1]);
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    acc[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra.a[k][b], b0, acc[b][0], 0, 0, 0);
+                    acc[b][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra.a[k][b], b1, acc[b][1], 0, 0, 0);
+                }
+            }
+        }
+        ra = rn;
+        i0 += 4;
+    } while (i0 < n && !__all(done));
+}
+
+// One distance of the sums below: 2 D values in, D values out.  (A template,
+// so that every index is a constant.)
+template <int D>
+__device__ __forceinline__ void halve_sums(float (&v)[32])
+{
+    const bool up = ((threadIdx.x & 63) & D) != 0;
+#pragma unroll
+    for (int q = 0; q < D; q++) {
+        const float give = up ? v[q] : v[q + D], keep = up ? v[q + D] : v[q];
+        v[q] = keep + __shfl_xor(give, D);
+    }
+}
+
+// The lane's outputs of receivers 16 B .. 16 B + 15 of the chunk (accumulator
+// layout as below), and the wave's partial sums of them: power, Re, Im.  Each
+// is the butterfly sum over the wave's 64 pixels (distance 32 first: a lane's
+// own two pixels), taken for the lane half's 8 receivers x (power, Re, Im, -)
+// together: at every distance a lane keeps half of the values and gives away
+// the other half, so each lane ends with one of the 32 sums (31 exchanges
+// instead of 5 for each of 24 values).
+template <int B>
+__device__ __forceinline__ void blend_store_rows(const floatx16 &a0, const floatx16 &a1, float *__restrict__ C,
+                                                 size_t P, const DevGrid &g, int j0, int nrx, int arow0, int acol,
+                                                 float (*s_red)[3])
+{
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+#pragma unroll
+    for (int pb = 0; pb < 2; pb++) {
+        const int arow = arow0 + 4 * pb;
+        if (arow < g.H && acol < g.W) {
+            float *out = C + (size_t)arow * g.W + acol;
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int jr = 16 * B + 4 * (r >> 2) + 2 * h + ((r >> 1) & 1);
+                if (jr < nrx) out[((size_t)(j0 + jr) * 2 + (r & 1)) * P] = pb ? a1[r] : a0[r];
+            }
+        }
+    }
+    float v[32];
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        const float x0 = a0[2 * q], y0 = a0[2 * q + 1], x1 = a1[2 * q], y1 = a1[2 * q + 1];
+        // (one explicit FMA, so every instantiation rounds the power alike)
+        v[4 * q] = fmaf(x0, x0, y0 * y0) + fmaf(x1, x1, y1 * y1);
+        v[4 * q + 1] = x0 + x1;
+        v[4 * q + 2] = y0 + y1;
+        v[4 * q + 3] = 0.f;
+    }
+    halve_sums<16>(v);
+    halve_sums<8>(v);
+    halve_sums<4>(v);
+    halve_sums<2>(v);
+    halve_sums<1>(v);
+    // the lane's value: index lane % 32 = 4 (receiver of the half) + component
+    const int q = (lane & 31) >> 2, c = lane & 3;
+    if (c < 3) s_red[16 * B + 4 * (q >> 1) + 2 * h + (q & 1)][c] = v[0];
 }
 
 // MARK (weights-only pass over chunks with no receivers): set live[b] for
@@ -2116,8 +2277,16 @@ __device__ __forceinline__ void blend_walk_multi(const BlendStage &st, const flo
 // same.  Otherwise, when live is given, positions of unmarked blocks read a
 // zero radiance: no pixel composites them, so their weight is zero and the
 // sums are unchanged.
-template <int R, bool SAVE, bool MARK = false, bool SECOND = false>
-__global__ __launch_bounds__(BLOCK) void k_blend_fwd_multi(const float4 *__restrict__ srec,
+//
+// Accumulator layout of a lane: pixels lane % 32 and 32 + lane % 32 of the
+// wave's sub-tile (register sets [.][0] and [.][1]); register r holds component
+// r % 2 of receiver 16 b + 4 (r / 4) + 2 (lane / 32) + (r / 2) % 2 of the chunk.
+//
+// (at least two waves per SIMD asked for, three with one register set: the
+// compiler then keeps the accumulators in ordinary registers; with the whole
+// file it puts them in accumulation registers and copies all 32 per group)
+template <int NB, bool SAVE, bool MARK = false, bool SECOND = false>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 2 : NB == 1 ? 3 : 5))) void k_blend_fwd_multi(const float4 *__restrict__ srec,
                                                      const uint32_t *__restrict__ pval,
                                                      const uint2 *__restrict__ ranges,
                                                      const float2 *__restrict__ rad,
@@ -2127,14 +2296,18 @@ __global__ __launch_bounds__(BLOCK) void k_blend_fwd_multi(const float4 *__restr
                                                      unsigned long long *__restrict__ stats,
                                                      const uint32_t *__restrict__ torder,
                                                      uint8_t *__restrict__ live, uint32_t *__restrict__ vflag,
-                                                     uint32_t mpos, FarState fs)
+                                                     uint32_t mpos, FarState fs, const int4 *__restrict__ vinfo,
+                                                     int nch)
 {
     constexpr bool redo = SECOND;
+    constexpr int NBX = NB > 0 ? NB : 1;
     __shared__ BlendStage st;
-    __shared__ float2 s_rad[R][BLOCK];
-    __shared__ float s_red[4][R][3];
+    // per staged entry: offset of its radiance (floats from the view's first
+    // position); top bit: none (past the prefix, or no pixel composites it)
+    __shared__ uint2 s_roff[MARK ? 1 : BLOCK];
+    __shared__ float s_red[4][MARK ? 1 : 16 * NBX][3];
     __shared__ unsigned char s_mark[MARK ? BLOCK : 1];
-    if (MARK) s_mark[threadIdx.x] = 0;
+    if (MARK) s_mark[threadIdx.x] = 0;   // (the staging's barriers come before its first use)
 
     // grid: (chunk, rank of the tile in its view's longest-first order)
     const int4 ch = chunks[blockIdx.x];
@@ -2158,9 +2331,13 @@ __global__ __launch_bounds__(BLOCK) void k_blend_fwd_multi(const float4 *__restr
     const int64_t view_end = ((int64_t)view + 1) * Kp;
 
     float T = 1.f;
-    float2 acc[R];
+    floatx16 acc[NBX][2];
 #pragma unroll
-    for (int r = 0; r < R; r++) acc[r] = make_float2(0.f, 0.f);
+    for (int b = 0; b < NBX; b++)
+#pragma unroll
+        for (int pb = 0; pb < 2; pb++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[b][pb][r] = 0.f;
     int last = 0;
     uint32_t ncomp = 0, neval = 0, nslot = 0;   // composited / evaluated while active / walked (SAVE)
     bool done = !inside;
@@ -2168,46 +2345,70 @@ __global__ __launch_bounds__(BLOCK) void k_blend_fwd_multi(const float4 *__restr
     const size_t pix = (size_t)row * g.W + col;
     int fcount = 0;
     uint2 *myrec = (!MARK && inside && mpos != 0xFFFFFFFFu) ? fs.rec + ((size_t)view * P + pix) * FAR_REC : nullptr;
+    // the view's radiance: (first row, rows), the chunk's first row and the
+    // lane's elements of an entry's run of rows (the lanes past the chunk's rows
+    // repeat its last one; their sums are not used)
+    int4 vr = make_int4(0, 1, 0, 0);
+    if (!MARK) {
+        vr = vinfo[view];
+        vr.x *= nch;
+        vr.y *= nch;
+    }
+    const float *rad_v = reinterpret_cast<const float *>(rad + (size_t)vr.x * Kp + (j0 - vr.x));
+    int rl[NBX];
+#pragma unroll
+    for (int b = 0; b < NBX; b++) rl[b] = min(32 * b + (lane & 31), 2 * nrx - 1);
+    // the lane's two accumulated pixels
+    const int h = lane >> 5, acol = tx * TILE + 8 * (wv & 1) + (lane & 7);
+    const int arow0 = ty * TILE + 8 * (wv >> 1) + ((lane & 31) >> 3);
 
-    if (deferred && inside) {
+    if (!MARK && deferred) {
         // the first pass's sums, then the view's recorded entries in list order
         // with each receiver's radiance (see k_blend_fwd1)
 #pragma unroll
-        for (int r = 0; r < R; r++)
-            if (r < nrx) {
-                acc[r].x = C[((size_t)(j0 + r) * 2) * P + pix];
-                acc[r].y = C[((size_t)(j0 + r) * 2 + 1) * P + pix];
-            }
-        const size_t q = (size_t)view * P + pix;
-        const int n = min((int)fs.cnt[q], FAR_REC);
-        for (int k = 0; k < n; k++) {
-            const uint2 rc = fs.rec[q * FAR_REC + k];
-            const float tw = __uint_as_float(rc.x);
-            const int64_t s = (int64_t)rc.y - (int64_t)view * Kp;
+        for (int pb = 0; pb < 2; pb++) {
+            const int arow = arow0 + 4 * pb;
+            if (arow >= g.H || acol >= g.W) continue;
+            const size_t apix = (size_t)arow * g.W + acol, q = (size_t)view * P + apix;
+            const int n = min((int)fs.cnt[q], FAR_REC);
 #pragma unroll
-            for (int r = 0; r < R; r++)
-                if (r < nrx) {
-                    const float2 sv = rad[(size_t)(j0 + r) * Kp + s];
-                    acc[r].x = fmaf(tw, sv.x, acc[r].x);
-                    acc[r].y = fmaf(tw, sv.y, acc[r].y);
+            for (int b = 0; b < NBX; b++)
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) {
+                    const int jr = 16 * b + 4 * (r >> 2) + 2 * h + ((r >> 1) & 1);
+                    if (jr >= nrx) continue;
+                    float x = C[((size_t)(j0 + jr) * 2) * P + apix], y = C[((size_t)(j0 + jr) * 2 + 1) * P + apix];
+                    for (int k = 0; k < n; k++) {
+                        const uint2 rc = fs.rec[q * FAR_REC + k];
+                        const float tw = __uint_as_float(rc.x);
+                        const float2 sv = rad[rad_index(vr, Kp, (int64_t)rc.y - (int64_t)view * Kp, j0 + jr)];
+                        x = fmaf(tw, sv.x, x);
+                        y = fmaf(tw, sv.y, y);
+                    }
+                    acc[b][pb][r] = x;
+                    acc[b][pb][r + 1] = y;
                 }
         }
     }
     for (uint32_t base = rg.x; !deferred && base < rg.y; base += BLOCK) {
         const uint32_t cnt = min((uint32_t)BLOCK, rg.y - base);
-        __syncthreads();
         uint32_t p = 0;
         bool nearp = true;
+        float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;
         if ((uint32_t)t < cnt) {
             p = min(pval[base + t], (uint32_t)(view_end - 1));
+            q0 = srec[2 * (size_t)p];
+            q1 = srec[2 * (size_t)p + 1];
             const int64_t s = max((int64_t)p - (int64_t)view * Kp, (int64_t)0);
             nearp = s < (int64_t)mpos;
-            const bool used = MARK || ((live == nullptr || live[p / MLP_PAIRS] != 0) && nearp);
-#pragma unroll
-            for (int r = 0; r < R; r++)
-                s_rad[r][t] = (r < nrx && used) ? rad[(size_t)(j0 + r) * Kp + s] : make_float2(0.f, 0.f);
+            if constexpr (!MARK) {
+                const bool used = (live == nullptr || live[p / MLP_PAIRS] != 0) && nearp;
+                const uint64_t o = (uint64_t)s * (uint64_t)(2 * vr.y);
+                s_roff[t] = used ? make_uint2((uint32_t)o, (uint32_t)(o >> 32)) : make_uint2(0u, 0x80000000u);
+            }
         }
-        stage_batch(st, srec, p, (uint32_t)t < cnt, tx, ty, g, nearp);
+        // (the vote at the end of a step orders its walks before this staging)
+        stage_batch(st, q0, q1, p, (uint32_t)t < cnt, tx, ty, g, nearp);
         if (__any(!done)) {
             const int n = __builtin_amdgcn_readfirstlane(st.len[wv]);
             const int lbase = (int)(base - rg.x) + 1;
@@ -2215,22 +2416,8 @@ __global__ __launch_bounds__(BLOCK) void k_blend_fwd_multi(const float4 *__restr
             const int i_far = __builtin_amdgcn_readfirstlane(st.ncnt[0][wv] + st.ncnt[1][wv] + st.ncnt[2][wv] +
                                                              st.ncnt[3][wv]);
             const bool wrap = __builtin_amdgcn_readfirstlane(st.wrap[wv]) != 0;
-            if (wrap)
-                blend_walk_multi<R, SAVE, true, MARK>(st, s_rad, wv, i_far, lbase, colf, rowf, Wf, halfW, T, acc,
-                                                      last, ncomp, neval, nslot, done, s_mark);
-            else
-                blend_walk_multi<R, SAVE, false, MARK>(st, s_rad, wv, i_far, lbase, colf, rowf, Wf, halfW, T, acc,
-                                                       last, ncomp, neval, nslot, done, s_mark);
-            if (i_far < n && __any(!done)) {
-                if (wrap)
-                    blend_walk_multi<R, SAVE, true, MARK, true>(st, s_rad, wv, n, lbase, colf, rowf, Wf, halfW, T, acc,
-                                                                last, ncomp, neval, nslot, done, s_mark, i_far,
-                                                                myrec, &fcount, fs.mark);
-                else
-                    blend_walk_multi<R, SAVE, false, MARK, true>(st, s_rad, wv, n, lbase, colf, rowf, Wf, halfW, T,
-                                                                 acc, last, ncomp, neval, nslot, done, s_mark, i_far,
-                                                                 myrec, &fcount, fs.mark);
-            }
+            blend_walk_mm<NB, SAVE, MARK>(st, s_roff, rad_v, rl, wv, i_far, n, lbase, wrap, colf, rowf, Wf, halfW, T, acc, last,
+                                          ncomp, neval, nslot, done, s_mark, myrec, fcount, fs.mark);
         }
         const int alldone = __syncthreads_and(done ? 1 : 0);
         if (MARK) {
@@ -2239,79 +2426,60 @@ __global__ __launch_bounds__(BLOCK) void k_blend_fwd_multi(const float4 *__restr
         }
         if (alldone) break;
     }
-    if (MARK) return;
-    if (!redo) {
-        // a pixel still open at the end of a view's truncated list: the view is redone in full
-        if (__syncthreads_or(inside && !done) && t == 0 && (vflag[view] & 1u)) atomicOr(vflag + view, 2u);
-        if (mpos != 0xFFFFFFFFu) {
-            // entries past the prefix composited here: records kept (8), or too many (4);
-            // every chunk of a view walks the same weights and writes the same records
-            if (inside) fs.cnt[(size_t)view * P + pix] = (uint8_t)min(fcount, 255);
-            const int any_rec = __syncthreads_or(fcount > 0 && fcount <= FAR_REC);
-            const int any_ovf = __syncthreads_or(fcount > FAR_REC);
-            if (t == 0) {
-                fs.tile[(size_t)view * g.tiles + tile] = any_rec ? 1 : 0;
-                if (any_ovf || any_rec) atomicOr(vflag + view, any_ovf ? 12u : 8u);
+    if constexpr (!MARK) {
+        if (!redo) {
+            // a pixel still open at the end of a view's truncated list: the view is redone in full
+            if (__syncthreads_or(inside && !done) && t == 0 && (vflag[view] & 1u)) atomicOr(vflag + view, 2u);
+            if (mpos != 0xFFFFFFFFu) {
+                // entries past the prefix composited here: records kept (8), or too many (4);
+                // every chunk of a view walks the same weights and writes the same records
+                if (inside) fs.cnt[(size_t)view * P + pix] = (uint8_t)min(fcount, 255);
+                const int any_rec = __syncthreads_or(fcount > 0 && fcount <= FAR_REC);
+                const int any_ovf = __syncthreads_or(fcount > FAR_REC);
+                if (t == 0) {
+                    fs.tile[(size_t)view * g.tiles + tile] = any_rec ? 1 : 0;
+                    if (any_ovf || any_rec) atomicOr(vflag + view, any_ovf ? 12u : 8u);
+                }
             }
         }
-    }
-
-    if (inside) {
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            if (r < nrx) {
-                C[((size_t)(j0 + r) * 2) * P + pix] = acc[r].x;
-                C[((size_t)(j0 + r) * 2 + 1) * P + pix] = acc[r].y;
-            }
-        }
-        if (SAVE && tslot >= 0) {
+        if (SAVE && inside && tslot >= 0) {
             Tfin[(size_t)tslot * P + pix] = T;
             nlast[(size_t)tslot * P + pix] = last;
         }
-    }
-    // per-tile partial sums: power, Re, Im (fixed-order reduction)
+        blend_store_rows<0>(acc[0][0], acc[0][1], C, P, g, j0, nrx, arow0, acol, s_red[wv]);
+        if constexpr (NB > 1) blend_store_rows<1>(acc[1][0], acc[1][1], C, P, g, j0, nrx, arow0, acol, s_red[wv]);
+        if (SAVE) {
+            const uint32_t nc = wave_sum_u32(ncomp), ne = wave_sum_u32(neval), ns = wave_sum_u32(nslot);
+            if (lane == 0) {
+                st.wcnt[0][wv] = (int)nc;
+                st.wcnt[1][wv] = (int)ne;
+                st.wcnt[2][wv] = (int)ns;
+            }
+        }
+        __syncthreads();
+        if (t < 16 * NBX * 3) {
+            const int r = t / 3, c = t % 3;
+            if (r < nrx) {
+                const float v = ((s_red[0][r][c] + s_red[1][r][c]) + s_red[2][r][c]) + s_red[3][r][c];
+                part[((size_t)(j0 + r) * g.tiles + tile) * 3 + c] = v;
+            }
+        }
+        // composited (pixel, entry) pairs: per chunk pixel and per receiver pixel,
+        // spread over STAT_SLOTS counters
+        if (SAVE && t == 0) {
+            const unsigned slot = (blockIdx.x + blockIdx.y * gridDim.x) % STAT_SLOTS;
+            unsigned long long n[3];
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const float pw = wave_sum_f32(fmaf(acc[r].x, acc[r].x, acc[r].y * acc[r].y));
-        const float sr = wave_sum_f32(acc[r].x);
-        const float si = wave_sum_f32(acc[r].y);
-        if (lane == 0) {
-            s_red[wv][r][0] = pw;
-            s_red[wv][r][1] = sr;
-            s_red[wv][r][2] = si;
-        }
-    }
-    if (SAVE) {
-        const uint32_t nc = wave_sum_u32(ncomp), ne = wave_sum_u32(neval), ns = wave_sum_u32(nslot);
-        if (lane == 0) {
-            st.wcnt[0][wv] = (int)nc;
-            st.wcnt[1][wv] = (int)ne;
-            st.wcnt[2][wv] = (int)ns;
-        }
-    }
-    __syncthreads();
-    if (t < R * 3) {
-        const int r = t / 3, c = t % 3;
-        if (r < nrx) {
-            const float v = ((s_red[0][r][c] + s_red[1][r][c]) + s_red[2][r][c]) + s_red[3][r][c];
-            part[((size_t)(j0 + r) * g.tiles + tile) * 3 + c] = v;
-        }
-    }
-    // composited (pixel, entry) pairs: per chunk pixel and per receiver pixel,
-    // spread over STAT_SLOTS counters
-    if (SAVE && t == 0) {
-        const unsigned slot = (blockIdx.x + blockIdx.y * gridDim.x) % STAT_SLOTS;
-        unsigned long long n[3];
-#pragma unroll
-        for (int c = 0; c < 3; c++)
-            n[c] = (unsigned long long)st.wcnt[c][0] + st.wcnt[c][1] + st.wcnt[c][2] + st.wcnt[c][3];
-        if (n[0]) {
-            atomicAdd(stats + slot, n[0]);
-            atomicAdd(stats + STAT_SLOTS + slot, n[0] * (unsigned long long)nrx);
-        }
-        if (n[2]) {
-            atomicAdd(stats + 2 * STAT_SLOTS + slot, n[1]);
-            atomicAdd(stats + 3 * STAT_SLOTS + slot, n[2]);
+            for (int c = 0; c < 3; c++)
+                n[c] = (unsigned long long)st.wcnt[c][0] + st.wcnt[c][1] + st.wcnt[c][2] + st.wcnt[c][3];
+            if (n[0]) {
+                atomicAdd(stats + slot, n[0]);
+                atomicAdd(stats + STAT_SLOTS + slot, n[0] * (unsigned long long)nrx);
+            }
+            if (n[2]) {
+                atomicAdd(stats + 2 * STAT_SLOTS + slot, n[1]);
+                atomicAdd(stats + 3 * STAT_SLOTS + slot, n[2]);
+            }
         }
     }
 }
@@ -2595,7 +2763,18 @@ hipError_t launch_rad_direct(const Scene &sc, Workspace &ws, hipStream_t st)
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_rad_direct, dim3(nblk(n)), dim3(BLOCK), 0, st, sc.rad.as<float2>(),
                        ws.vorder.as<uint32_t>(), ws.counters.as<unsigned long long>(),
-                       ws.d_rxview, ws.N, ws.Kp, ws.K, ws.rad.as<float2>());
+                       ws.d_rxview, ws.d_vinfo, ws.N, ws.Kp, ws.K, ws.rad.as<float2>());
+    return hipGetLastError();
+}
+
+hipError_t launch_rad_row(Workspace &ws, int j, float *out, hipStream_t st)
+{
+    const int v = ws.h_rxview[j];
+    int first = j, rows = 1;   // the view's rows are consecutive
+    while (first > 0 && ws.h_rxview[first - 1] == v) first--;
+    while (first + rows < ws.N && ws.h_rxview[first + rows] == v) rows++;
+    hipLaunchKernelGGL(k_rad_row, dim3(nblk((size_t)ws.Kp)), dim3(BLOCK), 0, st, ws.rad.as<float2>(),
+                       make_int4(first, rows, 0, 0), ws.Kp, j, reinterpret_cast<float2 *>(out));
     return hipGetLastError();
 }
 
@@ -2667,7 +2846,7 @@ hipError_t launch_mlp_pairs(const Scene &sc, const Mlp &m, Workspace &ws, hipStr
             hipLaunchKernelGGL(k_mlp_pairs_f32, dim3(blocks), dim3(BLOCK), 0, st, ws.Lp.as<float>(),
                                ws.Gp.as<float>(), m.w2a.as<float>(), m.tab.as<float4>(), b3,
                                ws.vorder.as<uint32_t>(), items, nmax, ws.Kp, ws.K,
-                               ws.counters.as<unsigned long long>(), ws.rad.as<float2>(), nlive);
+                               ws.counters.as<unsigned long long>(), ws.rad.as<float2>(), nlive, ws.d_vinfo);
         } else if (mlp_fused_ok(sc, m)) {
             // bound of the Gaussians' layer-1 term: per hidden unit
             // sum_c |W1[d, 36 + c]| max|f| + |b1[d]|, rounded up
@@ -2678,13 +2857,13 @@ hipError_t launch_mlp_pairs(const Scene &sc, const Mlp &m, Workspace &ws, hipStr
                                sc.feat.as<float>(), ws.Gp.as<float>(), m.w2h.as<half8>(), m.tabh.as<float4>(), b3,
                                m.w1h.as<half8>(), m.b1tab.as<float>(), std::ldexp(1.f, -m.w1exp), lbound,
                                ws.vorder.as<uint32_t>(), items, nmax, ws.Kp, ws.K,
-                               amax_words(ws), ws.rad.as<float2>(), nlive);
+                               amax_words(ws), ws.rad.as<float2>(), nlive, ws.d_vinfo);
         } else {
             hipLaunchKernelGGL(k_mlp_pairs<false>, dim3(blocks), dim3(BLOCK), 0, st, ws.Lp.as<float>(),
                                sc.feat.as<float>(), ws.Gp.as<float>(), m.w2h.as<half8>(), m.tabh.as<float4>(), b3,
                                m.w1h.as<half8>(), m.b1tab.as<float>(), 1.f, 0.f,
                                ws.vorder.as<uint32_t>(), items, nmax, ws.Kp, ws.K,
-                               amax_words(ws), ws.rad.as<float2>(), nlive);
+                               amax_words(ws), ws.rad.as<float2>(), nlive, ws.d_vinfo);
         }
     }
     return hipGetLastError();
@@ -2727,7 +2906,8 @@ hipError_t launch_count_items(Workspace &ws, bool far, unsigned long long *cnt, 
     return hipGetLastError();
 }
 
-template <int R>
+// NB = 0: one row per chunk; else chunks of at most 16 NB rows
+template <int NB>
 static void blend_launch(Workspace &ws, float *C, bool save, hipStream_t st, bool redo)
 {
     // the second pass blends overflowed views again with every position's
@@ -2736,7 +2916,7 @@ static void blend_launch(Workspace &ws, float *C, bool save, hipStream_t st, boo
     const FarState fs{ws.frec.as<uint2>(), ws.fcnt.as<uint8_t>(), ws.ftile.as<uint8_t>(), ws.live.as<uint8_t>()};
     dim3 grid((unsigned)ws.n_chunks, (unsigned)ws.g.tiles);
     const uint32_t *tord = ws.tiles_ordered ? ws.torder.as<uint32_t>() : nullptr;
-    if constexpr (R == 1) {
+    if constexpr (NB == 0) {
         grid.y = (unsigned)ws.g.tiles * 4;   // one workgroup per sub-tile
         const dim3 blk(BLEND1_THREADS);
         if (save)
@@ -2756,22 +2936,22 @@ static void blend_launch(Workspace &ws, float *C, bool save, hipStream_t st, boo
                                ws.vflag.as<uint32_t>(), mpos, fs);
     } else {
         if (save)
-            hipLaunchKernelGGL((k_blend_fwd_multi<R, true>), grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
+            hipLaunchKernelGGL((k_blend_fwd_multi<NB, true>), grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
                                ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.rad.as<float2>(),
                                ws.d_chunks, ws.Kp, ws.g, C, ws.Tfin.as<float>(), ws.nlast.as<int>(),
                                ws.part.as<float>(), stat_words(ws), tord, ws.lazy ? ws.live.as<uint8_t>() : nullptr,
-                               ws.vflag.as<uint32_t>(), mpos, fs);
+                               ws.vflag.as<uint32_t>(), mpos, fs, ws.d_vinfo, ws.Ch);
         else if (redo)
-            hipLaunchKernelGGL((k_blend_fwd_multi<R, false, false, true>), grid, dim3(BLOCK), 0, st,
+            hipLaunchKernelGGL((k_blend_fwd_multi<NB, false, false, true>), grid, dim3(BLOCK), 0, st,
                                ws.srec.as<float4>(), ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(),
                                ws.rad.as<float2>(), ws.d_chunks, ws.Kp, ws.g, C, nullptr, nullptr,
                                ws.part.as<float>(), nullptr, tord, ws.lazy ? ws.live.as<uint8_t>() : nullptr,
-                               ws.vflag.as<uint32_t>(), mpos, fs);
+                               ws.vflag.as<uint32_t>(), mpos, fs, ws.d_vinfo, ws.Ch);
         else
-            hipLaunchKernelGGL((k_blend_fwd_multi<R, false>), grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
+            hipLaunchKernelGGL((k_blend_fwd_multi<NB, false>), grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
                                ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.rad.as<float2>(),
                                ws.d_chunks, ws.Kp, ws.g, C, nullptr, nullptr, ws.part.as<float>(), nullptr, tord,
-                               ws.lazy ? ws.live.as<uint8_t>() : nullptr, ws.vflag.as<uint32_t>(), mpos, fs);
+                               ws.lazy ? ws.live.as<uint8_t>() : nullptr, ws.vflag.as<uint32_t>(), mpos, fs, ws.d_vinfo, ws.Ch);
     }
 }
 
@@ -2780,13 +2960,9 @@ hipError_t launch_blend_fwd(Workspace &ws, float *C, bool save, hipStream_t st, 
     if (ws.n_chunks == 0) return hipSuccess;
     // grid y limit (one workgroup per sub-tile with one receiver per chunk)
     if ((int64_t)ws.g.tiles * (ws.R == 1 ? 4 : 1) > 65535) return hipErrorInvalidConfiguration;
-    switch (ws.R) {
-    case 1: blend_launch<1>(ws, C, save, st, redo); break;
-    case 2: blend_launch<2>(ws, C, save, st, redo); break;
-    case 4: blend_launch<4>(ws, C, save, st, redo); break;
-    case 8: blend_launch<8>(ws, C, save, st, redo); break;
-    default: blend_launch<16>(ws, C, save, st, redo); break;
-    }
+    if (ws.R == 1) blend_launch<0>(ws, C, save, st, redo);
+    else if (ws.R <= 16) blend_launch<1>(ws, C, save, st, redo);
+    else blend_launch<2>(ws, C, save, st, redo);
     return hipGetLastError();
 }
 
@@ -2898,11 +3074,11 @@ hipError_t launch_blend_weights(Workspace &ws, hipStream_t st)
     if (ws.g.tiles > 65535) return hipErrorInvalidConfiguration;
     const uint32_t *tord = ws.tiles_ordered ? ws.torder.as<uint32_t>() : nullptr;
     if (ws.n_wchunks > 0)
-        hipLaunchKernelGGL((k_blend_fwd_multi<1, false, true>), dim3((unsigned)ws.n_wchunks, (unsigned)ws.g.tiles),
+        hipLaunchKernelGGL((k_blend_fwd_multi<0, false, true>), dim3((unsigned)ws.n_wchunks, (unsigned)ws.g.tiles),
                        dim3(BLOCK), 0, st, ws.srec.as<float4>(), ws.pval[ws.pairs_buf].as<uint32_t>(),
                        ws.ranges.as<uint2>(), ws.rad.as<float2>(), ws.d_wchunks, ws.Kp, ws.g, nullptr, nullptr,
                        nullptr, nullptr, nullptr, tord, ws.live.as<uint8_t>(), ws.vflag.as<uint32_t>(), 0xFFFFFFFFu,
-                       FarState{nullptr, nullptr, nullptr, nullptr});
+                       FarState{nullptr, nullptr, nullptr, nullptr}, nullptr, 1);
     if (ws.n_items > 0)
         hipLaunchKernelGGL(k_live_items, dim3(nblk(ws.n_items)), dim3(BLOCK), 0, st, ws.items.as<int4>(), ws.n_items,
                            ws.live.as<uint8_t>(), ws.Kp, ws.items_live.as<int4>(), live_count(ws));

@@ -968,6 +968,12 @@ static rxgs_status render_pass(rxgs_ctx *ctx, int mode, int Q, const float *tx, 
     int R = 1;
     if (shared_view)
         while (R < 16 && R < maxr) R *= 2;
+    // 32 rows per chunk (the entries staged and weighted once for them) when
+    // the launch stays large all the same; on a coverage map of 4,096 receivers
+    // (35,000 workgroups of 16 rows) the blend takes 0.60 instead of 0.67 ms,
+    // on a batch of 700 receivers of 16 transmitters (7,300 workgroups) 0.215
+    // instead of 0.207 ms
+    if (shared_view && !save && maxr >= 32 && (int64_t)(NR / 16) * g.tiles >= BLEND_WIDE_MIN) R = 32;
     ws.R = R;
     std::vector<int4> chunks;
     for (int v = 0; v < V; v++)
@@ -1818,7 +1824,7 @@ extern "C" rxgs_status rxgs_saved_export(const rxgs_saved *s, int what, void *ds
         break;
     case RXGS_EXPORT_PAIRS: n = (size_t)ws.D * 4; break;
     case RXGS_EXPORT_RANGES: n = (size_t)ws.V * ws.g.tiles * 8; break;
-    case RXGS_EXPORT_RADIANCE: src = ws.rad.p; n = (size_t)ws.N * ws.Kp * 8; break;
+    case RXGS_EXPORT_RADIANCE: n = (size_t)ws.N * ws.Kp * 8; break;
     case RXGS_EXPORT_TFINAL: src = ws.Tfin.p; n = (size_t)ws.n_tslots * P * 4; break;
     case RXGS_EXPORT_NLAST: src = ws.nlast.p; n = (size_t)ws.n_tslots * P * 4; break;
     case RXGS_EXPORT_RECORDS: src = ws.srec.p; n = VK * 32; break;
@@ -1879,6 +1885,23 @@ extern "C" rxgs_status rxgs_saved_export(const rxgs_saved *s, int what, void *ds
             HIPCHK(ctx, aux_copy(ctx, dst, out.data(), n, hipMemcpyHostToDevice));
         else
             std::memcpy(dst, out.data(), n);
+        return RXGS_OK;
+    }
+    if (what == RXGS_EXPORT_RADIANCE) {
+        // row by row (a view's rows lie position by position in the buffer)
+        hipStream_t a = nullptr;
+        HIPCHK(ctx, aux_stream(ctx, a));
+        DevBuf row;
+        if (!grow(row, (size_t)ws.Kp * 8, &ctx->alloc)) return fail(ctx, RXGS_E_OOM, "radiance row");
+        hipError_t e = hipSuccess;
+        for (int j = 0; j < ws.N && e == hipSuccess; j++) {
+            e = launch_rad_row(const_cast<Workspace &>(ws), j, row.as<float>(), a);
+            if (e == hipSuccess)
+                e = aux_copy(ctx, static_cast<char *>(dst) + (size_t)j * ws.Kp * 8, row.p, (size_t)ws.Kp * 8,
+                             dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost);
+        }
+        release(row);
+        HIPCHK(ctx, e);
         return RXGS_OK;
     }
     if (what == RXGS_EXPORT_NVIS) {

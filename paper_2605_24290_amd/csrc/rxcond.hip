@@ -359,7 +359,8 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_eval(
     const float *__restrict__ soa, int64_t K, const float *__restrict__ centres, const uint32_t *__restrict__ order,
     const int4 *__restrict__ items, int nitems, const int *__restrict__ nlive, int64_t Kp,
     const float2 *__restrict__ coef, const float4 *__restrict__ rab, const float4 *__restrict__ rloc,
-    const float4 *__restrict__ ctab, int lmax, int L, int n0, int C, int rpu, float2 *__restrict__ rad)
+    const float4 *__restrict__ ctab, int lmax, int L, int n0, int C, int rpu, float2 *__restrict__ rad,
+    const int4 *__restrict__ vinfo)
 {
     if (nlive) nitems = min(nitems, *nlive);
     __shared__ float4 s_ct[RC_TAB * RC_TAB];
@@ -375,6 +376,9 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_eval(
         if (ju >= nj) continue;
         const bool valid = pl < nvalid;
         const int64_t s = s0 + pl;
+        int4 vr = vinfo[view];   // its (first receiver, receivers), then rows
+        vr.x *= C;
+        vr.y *= C;
         const int64_t k = min((int64_t)order[(size_t)view * Kp + (valid ? s : s0)], K - 1);
         const float dx = soa[k] - centres[3 * view];
         const float dy = soa[K + k] - centres[3 * view + 1];
@@ -465,7 +469,7 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_eval(
                         const float4 lm = rloc[((size_t)j * Kp + s) * C + c];
                         const float sr = lm.x * xr[q] - lm.y * xi[q] + lm.z * br - lm.w * bi;
                         const float si = lm.x * xi[q] + lm.y * xr[q] + lm.z * bi + lm.w * br;
-                        rad[((size_t)j * C + c) * Kp + s] = make_float2(sr, si);
+                        rad[rad_index(vr, Kp, s, (int64_t)j * C + c)] = make_float2(sr, si);
                     }
                 }
             }
@@ -600,12 +604,12 @@ hipError_t launch_rxcond_pairs(const Scene &sc, const RxCond &m, Workspace &ws, 
         hipLaunchKernelGGL(k_rxcond_eval<RXGS_BASIS_FLE>, dim3(blocks), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,
                            ws.centres_p, ws.vorder.as<uint32_t>(), items, nmax, nlive, ws.Kp, m.coef.as<float2>(),
                            ws.rab.as<float4>(), ws.rloc.as<float4>(), m.ctab.as<float4>(), m.lmax, m.L, m.n0, m.C,
-                           rpu, ws.rad.as<float2>());
+                           rpu, ws.rad.as<float2>(), ws.d_vinfo);
     else
         hipLaunchKernelGGL(k_rxcond_eval<RXGS_BASIS_SH>, dim3(blocks), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,
                            ws.centres_p, ws.vorder.as<uint32_t>(), items, nmax, nlive, ws.Kp, m.coef.as<float2>(),
                            ws.rab.as<float4>(), ws.rloc.as<float4>(), m.ctab.as<float4>(), m.lmax, m.L, m.n0, m.C,
-                           rpu, ws.rad.as<float2>());
+                           rpu, ws.rad.as<float2>(), ws.d_vinfo);
     return hipGetLastError();
 }
 

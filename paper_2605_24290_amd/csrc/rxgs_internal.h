@@ -23,6 +23,7 @@ constexpr int HID = 64;
 constexpr int MLP_IN = ENC + FEAT;
 constexpr int MLP_RG = 16;               // receivers per MLP work item
 constexpr int MLP_PAIRS = 32;            // sorted positions per MLP work item
+constexpr int64_t BLEND_WIDE_MIN = 16384;   // workgroups of 16 rows from which a blend chunk holds 32 rows
 constexpr int LAZY_MIN_RX = 4;           // receivers of a TX view for its weights-only pass
 constexpr int64_t NEAR_LIMIT = 4096;     // nearest depth-sorted entries emitted per view first
 constexpr uint32_t PREFIX_POS = 4096;    // sorted positions whose radiance the first blend pass gets (TX)
@@ -222,7 +223,7 @@ struct Workspace {
     DevBuf torder;    // V x tiles u32: tiles by list length, longest first
     bool tiles_ordered = false;
     bool items_built = false;   // the MLP work items were expanded with the ranges
-    DevBuf rad;       // N x Kp float2
+    DevBuf rad;       // per view its rows x Kp float2, position by position (rad_index)
     DevBuf Lp;        // K x 64
     DevBuf Gp;        // N x 64
     DevBuf items;     // MLP work items (view, s0, first receiver, receivers | valid positions << 8)
@@ -396,6 +397,8 @@ uint32_t *emit_words(Workspace &ws);
 size_t emit_word_count(int V, int64_t Kp);
 hipError_t launch_ranges(Workspace &ws, const DevGrid &g, hipStream_t st);
 hipError_t launch_rad_direct(const Scene &sc, Workspace &ws, hipStream_t st);
+// row j of the radiance (Kp float2) into out, for exports
+hipError_t launch_rad_row(Workspace &ws, int j, float *out, hipStream_t st);
 hipError_t launch_mlp_global_term(const Mlp &m, Workspace &ws, hipStream_t st);
 hipError_t launch_mlp_items(Workspace &ws, hipStream_t st);
 hipError_t launch_mlp_local(const Scene &sc, const Mlp &m, Workspace &ws, hipStream_t st);
