@@ -73,29 +73,217 @@ __global__ void k_count_nonfinite(const float *__restrict__ p, size_t n, unsigne
     if (c) atomicAdd(cnt, c);
 }
 
-// largest |p[i]| as FP32 bits (non-negative floats order like their bits)
-__global__ void k_absmax_bits(const float *__restrict__ p, size_t n, unsigned *__restrict__ out)
+// Scene upload in one pass: AoS inputs -> SoA planes (x, y, z, ls0, ls1, ls2,
+// qw, qx, qy, qz, logit) and a copy of the radiance or features (src == dst:
+// already in place), with the checks the upload needs: per workgroup its
+// non-finite values and, as FP32 bits (non-negative floats order like their
+// bits), its largest |feature|.  The workgroups' words go straight to pinned
+// host memory, so the upload ends with one wait and no copy.  Bound by HBM: 43
+// floats read and written per Gaussian with features.  The checks' former
+// kernels read everything again and met in one atomic word (96 us of a 100k
+// upload).  An upload of 100k Gaussians with features 174 -> 26 us, of 1M 280 ->
+// 89 us (300 MB moved, 45 us of it in this kernel), of 1,000 84 -> 22 us.
+constexpr int UPLOAD_BLOCKS = 2048;
+
+__global__ __launch_bounds__(BLOCK) void k_scene_in(const float *__restrict__ means, const float *__restrict__ ls,
+                                                    const float *__restrict__ q, const float *__restrict__ lg,
+                                                    int64_t K, float *__restrict__ soa, const float *src, float *dst,
+                                                    size_t nrad, uint2 *__restrict__ out)
 {
-    size_t i = (size_t)blockIdx.x * BLOCK + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * BLOCK;
-    unsigned m = 0;
-    for (; i < n; i += stride) m = max(m, __float_as_uint(fabsf(p[i])));
+    __shared__ uint2 s_w[BLOCK / 64];
+    const size_t i0 = (size_t)blockIdx.x * BLOCK + threadIdx.x, stride = (size_t)gridDim.x * BLOCK;
+    unsigned bad = 0, top = 0;
+    for (size_t k = i0; k < (size_t)K; k += stride) {
+        float v[11];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
-    if ((threadIdx.x & 63) == 0 && m) atomicMax(out, m);
+        for (int a = 0; a < 3; a++) {
+            v[a] = means[3 * k + a];
+            v[3 + a] = ls[3 * k + a];
+        }
+#pragma unroll
+        for (int a = 0; a < 4; a++) v[6 + a] = q[4 * k + a];
+        v[10] = lg[k];
+#pragma unroll
+        for (int a = 0; a < 11; a++) {
+            bad += !isfinite(v[a]);
+            soa[(size_t)a * K + k] = v[a];
+        }
+    }
+    auto take = [&](float x) {
+        bad += !isfinite(x);
+        top = max(top, __float_as_uint(fabsf(x)));
+    };
+    // 16-byte accesses where both sides allow them
+    const bool wide = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
+    const size_t n4 = wide ? nrad / 4 : 0;
+    for (size_t i = i0; i < n4; i += 4 * stride) {
+        float4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            x[u] = i + u * stride < n4 ? reinterpret_cast<const float4 *>(src)[i + u * stride]
+                                       : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            take(x[u].x);
+            take(x[u].y);
+            take(x[u].z);
+            take(x[u].w);
+            if (src != dst && i + u * stride < n4) reinterpret_cast<float4 *>(dst)[i + u * stride] = x[u];
+        }
+    }
+    for (size_t i = 4 * n4 + i0; i < nrad; i += stride) {
+        const float x = src[i];
+        take(x);
+        if (src != dst) dst[i] = x;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        bad += (unsigned)__shfl_xor((int)bad, o);
+        top = max(top, (unsigned)__shfl_xor((int)top, o));
+    }
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = make_uint2(bad, top);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < BLOCK / 64; w++) {
+            bad += s_w[w].x;
+            top = max(top, s_w[w].y);
+        }
+        out[blockIdx.x] = make_uint2(bad, top);
+    }
 }
 
-// AoS inputs -> SoA planes (x, y, z, ls0, ls1, ls2, qw, qx, qy, qz, logit)
-__global__ void k_to_soa(const float *__restrict__ means, const float *__restrict__ ls,
-                         const float *__restrict__ q, const float *__restrict__ lg, int64_t K,
-                         float *__restrict__ soa)
+// What the host keeps of an uploaded MLP (written by k_mlp_tables).
+struct MlpInfo {
+    int bad;            // a parameter is not finite: nothing else was written
+    int exact;          // the rescaled layer-2 bias and layer-3 weights are exact
+    int b1_exact;       // the rescaled layer-1 bias is
+    int wexp, w1exp;    // powers of two of the split tables
+    float w1max;        // largest |W1[:, 36:]|
+    double w1abs[HID], b1abs[HID];   // per hidden unit, sum of |W1[:, 36:]| and |b1|
+};
+
+struct MlpTables {
+    float *raw, *w2a, *w2b, *tab, *tabh, *b1tab;
+    _Float16 *w2h, *w1h;
+};
+
+// The MLP's device tables (layouts at struct Mlp) from its flat parameters.
+// Every workgroup scans all of them (35 KB, from L2) for non-finite values and
+// the two largest weights, then writes its share of the tables; the first one
+// writes what the host keeps.  Before, the host read the parameters back,
+// built the tables and copied eight of them to the device: 155 us an upload,
+// now 22 us (6 us in this kernel, the rest the launch and the wait).
+constexpr int MLP_TABLE_BLOCKS = 8, MLP_TABLE_THREADS = 1024;
+
+__device__ __forceinline__ bool scaled_exact(float w, float x)
 {
-    const int64_t k = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (k >= K) return;
-    for (int a = 0; a < 3; a++) soa[a * K + k] = means[3 * k + a];
-    for (int a = 0; a < 3; a++) soa[(3 + a) * K + k] = ls[3 * k + a];
-    for (int a = 0; a < 4; a++) soa[(6 + a) * K + k] = q[4 * k + a];
-    soa[10 * K + k] = lg[k];
+    return isfinite(x) && !(w != 0.f && fabsf(x) < FLT_MIN);
+}
+
+__global__ __launch_bounds__(MLP_TABLE_THREADS) void k_mlp_tables(const float *__restrict__ p, MlpTables m, MlpInfo *info)
+{
+    __shared__ unsigned s_max[2];
+    __shared__ int s_exact, s_b1;
+    const int t = threadIdx.x;
+    const float *W1 = p, *b1 = p + HID * MLP_IN, *W2 = b1 + HID, *b2 = W2 + HID * HID, *W3 = b2 + HID;
+    if (t < 2) s_max[t] = 0u;
+    if (t == 0) s_exact = s_b1 = 1;
+    int bad = 0;
+    unsigned m2 = 0, m1 = 0;
+    constexpr int NT = MLP_TABLE_THREADS;
+#pragma unroll
+    for (int u = 0; u < (RXGS_MLP_NPARAM + NT - 1) / NT; u++) {
+        const int i = u * NT + t;
+        bad |= i < RXGS_MLP_NPARAM && !isfinite(p[i]);
+    }
+#pragma unroll
+    for (int u = 0; u < HID * HID / NT; u++) m2 = max(m2, __float_as_uint(fabsf(W2[u * NT + t])));
+#pragma unroll
+    for (int u = 0; u < HID * FEAT / NT; u++) {
+        const int i = u * NT + t;
+        m1 = max(m1, __float_as_uint(fabsf(W1[(i / FEAT) * MLP_IN + ENC + i % FEAT])));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        m2 = max(m2, (unsigned)__shfl_xor((int)m2, o));
+        m1 = max(m1, (unsigned)__shfl_xor((int)m1, o));
+    }
+    if (__syncthreads_or(bad)) {
+        if (blockIdx.x == 0 && t == 0) info->bad = 1;
+        return;
+    }
+    if ((t & 63) == 0) {
+        atomicMax(&s_max[0], m2);
+        atomicMax(&s_max[1], m1);
+    }
+    __syncthreads();
+    const float wmax = __uint_as_float(s_max[0]), w1max = __uint_as_float(s_max[1]);
+    // W2 and the feature block of W1 are scaled by an exact power of two so
+    // that their largest entry lands just under 2^15 (FP16 range, and the low
+    // halves stay out of the subnormal range); the scale is undone exactly in
+    // the biases and the layer-3 weights
+    int e2 = 0, e1 = 0;
+    if (wmax > 0.f) (void)frexpf(wmax, &e2);   // wmax < 2^e2
+    if (w1max > 0.f) (void)frexpf(w1max, &e1);
+    const int wexp = min(max(15 - e2, -120), 120), w1exp = min(max(15 - e1, -120), 120);
+    const int i0 = blockIdx.x * NT + t, stride = gridDim.x * NT;
+    for (int i = i0; i < RXGS_MLP_NPARAM; i += stride) m.raw[i] = p[i];
+    // MFMA A-operand layouts of W2 (forward) and W2^T (backward)
+    for (int i = i0; i < 2 * 32 * 64; i += stride) {
+        const int l = i & 63, tt = (i >> 6) & 31, mb = i >> 11;
+        m.w2a[i] = W2[(32 * mb + (l & 31)) * HID + hid_of(l >> 5, tt)];
+        m.w2b[i] = W2[hid_of(l >> 5, tt) * HID + 32 * mb + (l & 31)];
+    }
+    // the split copies: hi = FP16(w 2^e), lo = FP16(w 2^e - hi)
+    for (int i = i0; i < 2 * 4 * 64 * 8; i += stride) {
+        const int el = i & 7, l = (i >> 3) & 63, q = (i >> 9) & 3, mb = i >> 11;
+        const float w = ldexpf(W2[(32 * mb + (l & 31)) * HID + hid_of(l >> 5, 8 * q + el)], wexp);
+        const _Float16 hi = (_Float16)w;
+        m.w2h[i] = hi;
+        m.w2h[2 * 4 * 64 * 8 + i] = (_Float16)(w - (float)hi);
+    }
+    for (int i = i0; i < 2 * 2 * 64 * 8; i += stride) {
+        const int el = i & 7, l = (i >> 3) & 63, q = (i >> 9) & 1, mb = i >> 10;
+        const float w = ldexpf(W1[(32 * mb + (l & 31)) * MLP_IN + ENC + 16 * q + 8 * (l >> 5) + el], w1exp);
+        const _Float16 hi = (_Float16)w;
+        m.w1h[i] = hi;
+        m.w1h[2 * 2 * 64 * 8 + i] = (_Float16)(w - (float)hi);
+    }
+    if (blockIdx.x != 0) return;
+    if (t < 64) {
+        // per (lane half, block, accumulator register): hidden unit d and its
+        // layer-3 weights and layer-2 bias; b1 in the accumulator order
+        const int hh = t >> 5, mb = (t >> 4) & 1, r = t & 15;
+        const int d = 32 * mb + 8 * (r / 4) + 4 * hh + (r % 4);
+        const float v[3] = {W3[d], W3[HID + d], b2[d]};
+        bool ok = true;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const float x = ldexpf(v[c], c < 2 ? -wexp : wexp);
+            ok = ok && scaled_exact(v[c], x);
+            m.tab[4 * t + c] = v[c];
+            m.tabh[4 * t + c] = x;
+        }
+        m.tab[4 * t + 3] = 0.f;
+        m.tabh[4 * t + 3] = 0.f;
+        if (!ok) atomicAnd(&s_exact, 0);
+        const float b = b1[hid_of(t >> 5, t & 31)], x = ldexpf(b, w1exp);
+        m.b1tab[t] = x;
+        if (!scaled_exact(b, x)) atomicAnd(&s_b1, 0);
+        double a = 0.0;
+        for (int c = 0; c < FEAT; c++) a += fabs((double)W1[t * MLP_IN + ENC + c]);
+        info->w1abs[t] = a;
+        info->b1abs[t] = fabs((double)b1[t]);
+    }
+    __syncthreads();
+    if (t == 0) {
+        info->exact = s_exact;
+        info->b1_exact = s_b1;
+        info->wexp = wexp;
+        info->w1exp = w1exp;
+        info->w1max = w1max;
+        info->bad = 0;
+    }
 }
 
 bool all_finite_host(const float *p, size_t n)
@@ -433,6 +621,11 @@ rxgs_status setup_noalloc(rxgs_ctx *ctx)
     HIPCHK(ctx, hipEventCreateWithFlags(&ws.staged, hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreateWithFlags(&ws.counted, hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreateWithFlags(&ws.done, hipEventDisableTiming));
+    e = hipHostMalloc(&ctx->h_upload, std::max(sizeof(uint2) * UPLOAD_BLOCKS, sizeof(MlpInfo)), hipHostMallocDefault);
+    if (e != hipSuccess) {
+        ctx->h_upload = nullptr;
+        return hip_fail(ctx, e, "pinned words of the uploads");
+    }
     return RXGS_OK;
 }
 }  // namespace
@@ -538,6 +731,7 @@ extern "C" void rxgs_destroy(rxgs_ctx *ctx)
         delete ctx->noalloc;
         ctx->noalloc = nullptr;
     }
+    if (ctx->h_upload) (void)hipHostFree(ctx->h_upload);
     if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
     delete ctx;
 }
@@ -583,7 +777,6 @@ extern "C" rxgs_status rxgs_scene_upload(rxgs_ctx *ctx, int64_t K, const float *
     const bool geo = !feat && !radiance;   // geometry only: radiance from a conditioning model
     const size_t nrad = geo ? 0 : (size_t)K * (feat ? FEAT : 2);
     const float *radsrc = feat ? features : radiance;
-    const hipMemcpyKind kind = src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     if (!src_on_device) {
         if (!all_finite_host(means, 3 * K) || !all_finite_host(log_scales, 3 * K) ||
             !all_finite_host(quats, 4 * K) || !all_finite_host(logits, K) || !all_finite_host(radsrc, nrad))
@@ -595,37 +788,36 @@ extern "C" rxgs_status rxgs_scene_upload(rxgs_ctx *ctx, int64_t K, const float *
         }
     }
     GROW(ctx, sc.soa, (size_t)11 * std::max<int64_t>(K, 1) * 4);
-    GROW(ctx, ctx->stage, (size_t)12 * std::max<int64_t>(K, 1) * 4 + 256);
-    float *stg = ctx->stage.as<float>();
-    if (K > 0) {
-        HIPCHK(ctx, hipMemcpyAsync(stg, means, 12 * K, kind, st));
-        HIPCHK(ctx, hipMemcpyAsync(stg + 3 * K, log_scales, 12 * K, kind, st));
-        HIPCHK(ctx, hipMemcpyAsync(stg + 6 * K, quats, 16 * K, kind, st));
-        HIPCHK(ctx, hipMemcpyAsync(stg + 10 * K, logits, 4 * K, kind, st));
-        hipLaunchKernelGGL(k_to_soa, dim3((unsigned)((K + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, st, stg, stg + 3 * K,
-                           stg + 6 * K, stg + 10 * K, K, sc.soa.as<float>());
-        HIPCHK(ctx, hipGetLastError());
-    }
     DevBuf &dst = feat ? sc.feat : sc.rad;
     GROW(ctx, dst, std::max<size_t>(nrad, 1) * 4);
-    if (K > 0 && nrad > 0) HIPCHK(ctx, hipMemcpyAsync(dst.p, radsrc, nrad * 4, kind, st));
     float fmax = 0.f;   // largest |feature|, for the split-FP16 layer-1 path
-    if (src_on_device && K > 0) {
-        unsigned *cnt = reinterpret_cast<unsigned *>(stg + 11 * K);
-        HIPCHK(ctx, hipMemsetAsync(cnt, 0, 8, st));
-        const unsigned blocks = (unsigned)std::min<int64_t>((11 * K + BLOCK - 1) / BLOCK, 2048);
-        hipLaunchKernelGGL(k_count_nonfinite, dim3(blocks), dim3(BLOCK), 0, st, sc.soa.as<float>(), (size_t)11 * K,
-                           cnt);
-        hipLaunchKernelGGL(k_count_nonfinite, dim3(blocks), dim3(BLOCK), 0, st, dst.as<float>(), nrad, cnt);
-        if (feat) hipLaunchKernelGGL(k_absmax_bits, dim3(blocks), dim3(BLOCK), 0, st, dst.as<float>(), nrad, cnt + 1);
+    if (K > 0) {
+        const float *src[4] = {means, log_scales, quats, logits};
+        if (!src_on_device) {
+            GROW(ctx, ctx->stage, (size_t)11 * K * 4);
+            float *stg = ctx->stage.as<float>();
+            const size_t len[4] = {3, 3, 4, 1};
+            for (int a = 0; a < 4; a++) {
+                HIPCHK(ctx, hipMemcpyAsync(stg, src[a], len[a] * K * 4, hipMemcpyHostToDevice, st));
+                src[a] = stg;
+                stg += len[a] * K;
+            }
+            if (nrad > 0) HIPCHK(ctx, hipMemcpyAsync(dst.p, radsrc, nrad * 4, hipMemcpyHostToDevice, st));
+            radsrc = dst.as<float>();
+        }
+        const int64_t work = std::max<int64_t>(K, (int64_t)nrad / 16);   // (four 16-byte pieces a thread)
+        const unsigned blocks = (unsigned)std::min<int64_t>((work + BLOCK - 1) / BLOCK, UPLOAD_BLOCKS);
+        uint2 *part = static_cast<uint2 *>(ctx->h_upload);
+        hipLaunchKernelGGL(k_scene_in, dim3(blocks), dim3(BLOCK), 0, st, src[0], src[1], src[2], src[3], K,
+                           sc.soa.as<float>(), radsrc, dst.as<float>(), nrad, part);
         HIPCHK(ctx, hipGetLastError());
-        unsigned h[2] = {0, 0};
-        HIPCHK(ctx, hipMemcpyAsync(h, cnt, 8, hipMemcpyDeviceToHost, st));
         HIPCHK(ctx, hipStreamSynchronize(st));
-        if (h[0]) return fail(ctx, RXGS_E_INVALID, "non-finite value in the scene");
-        std::memcpy(&fmax, &h[1], 4);
-    } else if (feat) {
-        for (size_t i = 0; i < nrad; i++) fmax = std::max(fmax, std::fabs(radsrc[i]));
+        unsigned top = 0;
+        for (unsigned i = 0; i < blocks; i++) {
+            if (part[i].x) return fail(ctx, RXGS_E_INVALID, "non-finite value in the scene");
+            top = std::max(top, part[i].y);
+        }
+        if (feat) std::memcpy(&fmax, &top, 4);
     }
     sc.fmax = fmax;
     sc.K = K;
@@ -643,141 +835,44 @@ extern "C" rxgs_status rxgs_mlp_upload(rxgs_ctx *ctx, const float *params, int s
     if (!params) return fail(ctx, RXGS_E_INVALID, "params is NULL");
     DeviceScope ds(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    std::vector<float> h(RXGS_MLP_NPARAM);
-    if (src_on_device) {
-        HIPCHK(ctx, hipMemcpyAsync(h.data(), params, sizeof(float) * h.size(), hipMemcpyDeviceToHost, st));
-        HIPCHK(ctx, hipStreamSynchronize(st));
-    } else {
-        std::memcpy(h.data(), params, sizeof(float) * h.size());
-    }
-    if (!all_finite_host(h.data(), h.size())) return fail(ctx, RXGS_E_INVALID, "non-finite MLP parameter");
-    const float *W2 = h.data() + HID * MLP_IN + HID;
-    const float *b2 = W2 + HID * HID;
-    const float *W3 = b2 + HID;
-    // MFMA A-operand layouts of W2 (forward) and W2^T (backward):
-    //   w2a[mb][t][lane] = W2[32 mb + lane % 32][hid_of(lane / 32, t)]
-    //   w2b[ib][t][lane] = W2[hid_of(lane / 32, t)][32 ib + lane % 32]
-    std::vector<float> w2a(2 * 32 * 64), w2b(2 * 32 * 64);
-    for (int mb = 0; mb < 2; mb++)
-        for (int t = 0; t < 32; t++)
-            for (int l = 0; l < 64; l++) {
-                w2a[(mb * 32 + t) * 64 + l] = W2[(32 * mb + (l & 31)) * HID + hid_of(l >> 5, t)];
-                w2b[(mb * 32 + t) * 64 + l] = W2[hid_of(l >> 5, t) * HID + 32 * mb + (l & 31)];
-            }
-    // per (lane half h, block mb, accumulator register r): hidden index d and
-    // its layer-3 weights and layer-2 bias
-    std::vector<float> tab(2 * 2 * 16 * 4, 0.f);
-    for (int hh = 0; hh < 2; hh++)
-        for (int mb = 0; mb < 2; mb++)
-            for (int r = 0; r < 16; r++) {
-                const int d = 32 * mb + 8 * (r / 4) + 4 * hh + (r % 4);
-                float *e = &tab[((hh * 2 + mb) * 16 + r) * 4];
-                e[0] = W3[d];
-                e[1] = W3[HID + d];
-                e[2] = b2[d];
-            }
-    // split-FP16 copy of W2 for the forward pair kernel: W2 is scaled by an
-    // exact power of two so that its largest entry lands just under 2^15
-    // (FP16 range, and the low halves stay out of the subnormal range); the
-    // scale is undone exactly in the layer-2 bias and the layer-3 weights.
-    float wmax = 0.f;
-    for (int i = 0; i < HID * HID; i++) wmax = std::max(wmax, std::fabs(W2[i]));
-    int e = 0;
-    if (wmax > 0.f) std::frexp(wmax, &e);   // wmax < 2^e
-    const int wexp = std::min(std::max(15 - e, -120), 120);
-    std::vector<_Float16> w2h(2 * 2 * 4 * 64 * 8);
-    for (int mb = 0; mb < 2; mb++)
-        for (int q = 0; q < 4; q++)
-            for (int l = 0; l < 64; l++)
-                for (int i = 0; i < 8; i++) {
-                    const float w = std::ldexp(W2[(32 * mb + (l & 31)) * HID + hid_of(l >> 5, 8 * q + i)], wexp);
-                    const _Float16 hi = (_Float16)w;
-                    const _Float16 lo = (_Float16)(w - (float)hi);
-                    w2h[(((0 * 2 + mb) * 4 + q) * 64 + l) * 8 + i] = hi;
-                    w2h[(((1 * 2 + mb) * 4 + q) * 64 + l) * 8 + i] = lo;
-                }
-    // split-FP16 copy of the feature block of W1 for computing the Gaussians'
-    // layer-1 term inside the pair kernel: W1[:, 36:] * 2^w1exp (largest entry
-    // just under 2^15) as FP16 (hi, lo) pairs in the MFMA 32x32x16 A-operand
-    // layout, [2 part][2 mb][2 q][64 lane] x 8 halves, element i =
-    // W1[32 mb + lane % 32][36 + 16 q + 8 (lane / 32) + i]; b1 in the
-    // accumulator order of each lane half; per-row sums of |W1[:, 36:]|
-    const float *W1 = h.data();
-    const float *b1 = W1 + HID * MLP_IN;
-    float w1max = 0.f;
-    for (int d = 0; d < HID; d++)
-        for (int c = 0; c < FEAT; c++) w1max = std::max(w1max, std::fabs(W1[d * MLP_IN + ENC + c]));
-    int e1 = 0;
-    if (w1max > 0.f) std::frexp(w1max, &e1);
-    const int w1exp = std::min(std::max(15 - e1, -120), 120);
-    std::vector<_Float16> w1h(2 * 2 * 2 * 64 * 8);
-    for (int mb = 0; mb < 2; mb++)
-        for (int q = 0; q < 2; q++)
-            for (int l = 0; l < 64; l++)
-                for (int i = 0; i < 8; i++) {
-                    const float w = std::ldexp(W1[(32 * mb + (l & 31)) * MLP_IN + ENC + 16 * q + 8 * (l >> 5) + i],
-                                               w1exp);
-                    const _Float16 hi = (_Float16)w;
-                    const _Float16 lo = (_Float16)(w - (float)hi);
-                    w1h[(((0 * 2 + mb) * 2 + q) * 64 + l) * 8 + i] = hi;
-                    w1h[(((1 * 2 + mb) * 2 + q) * 64 + l) * 8 + i] = lo;
-                }
-    std::vector<float> b1tab(2 * 32);
-    bool b1_exact = true;
-    for (int hh = 0; hh < 2; hh++)
-        for (int t = 0; t < 32; t++) {
-            const float x = std::ldexp(b1[hid_of(hh, t)], w1exp);
-            if (!std::isfinite(x) || (b1[hid_of(hh, t)] != 0.f && std::fabs(x) < FLT_MIN)) b1_exact = false;
-            b1tab[hh * 32 + t] = x;
-        }
-    std::vector<double> w1abs(HID);
-    for (int d = 0; d < HID; d++) {
-        double r = 0.0;
-        for (int c = 0; c < FEAT; c++) r += std::fabs((double)W1[d * MLP_IN + ENC + c]);
-        w1abs[d] = r;
-    }
-
-    // the rescaled layer-2 bias and layer-3 weights must stay finite and
-    // normal (an exact rescaling); otherwise layer 2 runs on FP32 MFMA
-    std::vector<float> tabh(tab);
-    bool exact = true;
-    for (size_t i = 0; i < tabh.size(); i += 4) {
-        for (int c = 0; c < 3; c++) {
-            const float x = std::ldexp(tab[i + c], c < 2 ? -wexp : wexp);
-            if (!std::isfinite(x) || (tab[i + c] != 0.f && std::fabs(x) < FLT_MIN)) exact = false;
-            tabh[i + c] = x;
-        }
-    }
     Mlp &m = ctx->mlp;
-    m.valid = false;
-    const char *env = std::getenv("RXGS_MLP_FP32");
-    m.fp32 = !exact || (env && env[0] == '1');
-    m.wexp = wexp;
-    m.w1exp = w1exp;
-    m.w1_ok = b1_exact && w1max < 32768.f;
-    for (int d = 0; d < HID; d++) {
-        m.w1abs[d] = w1abs[d];
-        m.b1abs[d] = std::fabs((double)b1[d]);
+    if (!src_on_device) {
+        GROW(ctx, ctx->stage, sizeof(float) * RXGS_MLP_NPARAM);
+        HIPCHK(ctx, hipMemcpyAsync(ctx->stage.p, params, sizeof(float) * RXGS_MLP_NPARAM, hipMemcpyHostToDevice, st));
+        params = ctx->stage.as<float>();
     }
-    GROW(ctx, m.w1h, sizeof(_Float16) * w1h.size());
-    GROW(ctx, m.b1tab, sizeof(float) * b1tab.size());
-    HIPCHK(ctx, hipMemcpyAsync(m.w1h.p, w1h.data(), sizeof(_Float16) * w1h.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(ctx, hipMemcpyAsync(m.b1tab.p, b1tab.data(), sizeof(float) * b1tab.size(), hipMemcpyHostToDevice, st));
-    GROW(ctx, m.w2h, sizeof(_Float16) * w2h.size());
-    GROW(ctx, m.tabh, sizeof(float) * tabh.size());
-    HIPCHK(ctx, hipMemcpyAsync(m.w2h.p, w2h.data(), sizeof(_Float16) * w2h.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(ctx, hipMemcpyAsync(m.tabh.p, tabh.data(), sizeof(float) * tabh.size(), hipMemcpyHostToDevice, st));
+    GROW(ctx, m.w1h, sizeof(_Float16) * 2 * 2 * 2 * 64 * 8);
+    GROW(ctx, m.b1tab, sizeof(float) * 2 * 32);
+    GROW(ctx, m.w2h, sizeof(_Float16) * 2 * 2 * 4 * 64 * 8);
+    GROW(ctx, m.tabh, sizeof(float) * 2 * 2 * 16 * 4);
     GROW(ctx, m.raw, sizeof(float) * RXGS_MLP_NPARAM);
-    GROW(ctx, m.w2a, sizeof(float) * w2a.size());
-    GROW(ctx, m.w2b, sizeof(float) * w2b.size());
-    GROW(ctx, m.tab, sizeof(float) * tab.size());
-    HIPCHK(ctx, hipMemcpyAsync(m.raw.p, h.data(), sizeof(float) * h.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(ctx, hipMemcpyAsync(m.w2a.p, w2a.data(), sizeof(float) * w2a.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(ctx, hipMemcpyAsync(m.w2b.p, w2b.data(), sizeof(float) * w2b.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(ctx, hipMemcpyAsync(m.tab.p, tab.data(), sizeof(float) * tab.size(), hipMemcpyHostToDevice, st));
+    GROW(ctx, m.w2a, sizeof(float) * 2 * 32 * 64);
+    GROW(ctx, m.w2b, sizeof(float) * 2 * 32 * 64);
+    GROW(ctx, m.tab, sizeof(float) * 2 * 2 * 16 * 4);
+    MlpInfo *info = static_cast<MlpInfo *>(ctx->h_upload);
+    info->bad = 1;
+    const bool was_valid = m.valid;
+    m.valid = false;
+    const MlpTables tabs = {m.raw.as<float>(),  m.w2a.as<float>(),   m.w2b.as<float>(),      m.tab.as<float>(),
+                            m.tabh.as<float>(), m.b1tab.as<float>(), m.w2h.as<_Float16>(), m.w1h.as<_Float16>()};
+    hipLaunchKernelGGL(k_mlp_tables, dim3(MLP_TABLE_BLOCKS), dim3(MLP_TABLE_THREADS), 0, st, params, tabs, info);
+    HIPCHK(ctx, hipGetLastError());
     // (ordered after earlier work on the caller's stream that may still read
-    // the old tables; the host vectors must outlive the copies)
+    // the old tables)
     HIPCHK(ctx, hipStreamSynchronize(st));
+    if (info->bad) {
+        m.valid = was_valid;   // the former MLP is untouched
+        return fail(ctx, RXGS_E_INVALID, "non-finite MLP parameter");
+    }
+    const char *env = std::getenv("RXGS_MLP_FP32");
+    m.fp32 = !info->exact || (env && env[0] == '1');
+    m.wexp = info->wexp;
+    m.w1exp = info->w1exp;
+    m.w1_ok = info->b1_exact && info->w1max < 32768.f;
+    for (int d = 0; d < HID; d++) {
+        m.w1abs[d] = info->w1abs[d];
+        m.b1abs[d] = info->b1abs[d];
+    }
     m.version = ++ctx->version_counter;
     m.valid = true;
     return RXGS_OK;

@@ -318,7 +318,8 @@ struct rxgs_ctx {
     rxgs::Mlp mlp;
     rxgs::RxCond rxc;       // conditioning model of the paper's radiance path
     rxgs::Workspace ws;     // used when the caller passes no saved state
-    rxgs::DevBuf stage;     // scene upload staging
+    rxgs::DevBuf stage;     // device staging of uploads from host memory
+    void *h_upload = nullptr;   // pinned: what the upload kernels report
     std::string err;
     uint64_t version_counter = 0;
     std::vector<rxgs_saved *> saved;   // live saved states
