@@ -50,7 +50,7 @@ class RxRenderFn(torch.autograd.Function):
                 renderer.upload_mlp(mlp.detach())
                 renderer._autograd_mlp = mstamp
                 renderer._autograd_keep_mlp = mlp
-        saved = rxgs.Saved(renderer)
+        saved = renderer._take_state()   # (of an earlier step whose backward has run, if there is one)
         C, P, _ = renderer.render(rx.detach(), tx=None if tx is None else tx.detach(), rx_off=rx_off, mode=mode,
                                   saved=saved)
         ctx.renderer = renderer
@@ -67,7 +67,7 @@ class RxRenderFn(torch.autograd.Function):
         if gC is None:
             gC = torch.zeros_like(C)
         g = r.backward(ctx.saved_state, C, gC.contiguous(), None if gP is None else gP.contiguous())
-        ctx.saved_state.close()
+        r._return_state(ctx.saved_state)
         fr = g["features"] if ctx.use_mlp else g["radiance"]
         gm = g["mlp"] if ctx.use_mlp else None
         return (None, None, None, g["means"], g["log_scales"], g["quats"], g["logits"], fr, gm, None, None)

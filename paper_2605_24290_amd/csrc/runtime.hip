@@ -611,21 +611,19 @@ rxgs_status setup_noalloc(rxgs_ctx *ctx)
     s->ws.al = &ctx->fixed;
     ctx->noalloc = s;
     Workspace &ws = s->ws;
-    e = hipHostMalloc(&ws.h_pinned, NOALLOC_PINNED, hipHostMallocDefault);
+    // (one pinned block: the workspace's staging, then the upload kernels' words)
+    e = hipHostMalloc(&ws.h_pinned, NOALLOC_PINNED + std::max(sizeof(uint2) * UPLOAD_BLOCKS, sizeof(MlpInfo)),
+                      hipHostMallocDefault);
     if (e != hipSuccess) {
         ws.h_pinned = nullptr;
         return hip_fail(ctx, e, "pinned staging of the allocation-free workspace");
     }
     ws.h_pinned_cap = NOALLOC_PINNED;
+    ctx->h_upload = static_cast<char *>(ws.h_pinned) + NOALLOC_PINNED;
     ws.fixed_host = true;
     HIPCHK(ctx, hipEventCreateWithFlags(&ws.staged, hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreateWithFlags(&ws.counted, hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreateWithFlags(&ws.done, hipEventDisableTiming));
-    e = hipHostMalloc(&ctx->h_upload, std::max(sizeof(uint2) * UPLOAD_BLOCKS, sizeof(MlpInfo)), hipHostMallocDefault);
-    if (e != hipSuccess) {
-        ctx->h_upload = nullptr;
-        return hip_fail(ctx, e, "pinned words of the uploads");
-    }
     return RXGS_OK;
 }
 }  // namespace
@@ -731,7 +729,6 @@ extern "C" void rxgs_destroy(rxgs_ctx *ctx)
         delete ctx->noalloc;
         ctx->noalloc = nullptr;
     }
-    if (ctx->h_upload) (void)hipHostFree(ctx->h_upload);
     if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
     delete ctx;
 }

@@ -319,7 +319,7 @@ struct rxgs_ctx {
     rxgs::RxCond rxc;       // conditioning model of the paper's radiance path
     rxgs::Workspace ws;     // used when the caller passes no saved state
     rxgs::DevBuf stage;     // device staging of uploads from host memory
-    void *h_upload = nullptr;   // pinned: what the upload kernels report
+    void *h_upload = nullptr;   // pinned: what the upload kernels report (in noalloc's staging block)
     std::string err;
     uint64_t version_counter = 0;
     std::vector<rxgs_saved *> saved;   // live saved states

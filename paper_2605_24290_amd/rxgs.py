@@ -213,11 +213,12 @@ def _ptr(t):
 class Saved:
     """Forward state kept for the backward pass (rxgs_saved)."""
 
-    def __init__(self, renderer: "Renderer"):
+    def __init__(self, renderer: "Renderer", _h=None):
         self.renderer = renderer
-        h = c_void_p()
-        _check(lib().rxgs_saved_create(renderer._ctx, byref(h)), renderer._ctx)
-        self._h = h
+        if _h is None:
+            _h = c_void_p()
+            _check(lib().rxgs_saved_create(renderer._ctx, byref(_h)), renderer._ctx)
+        self._h = _h
 
     def info(self) -> dict:
         i = CSavedInfo()
@@ -303,6 +304,55 @@ class Renderer:
         self._ctx = ctx
         self.K = 0
         self.use_mlp = False
+        self._idle = []   # finished forward states of the autograd function: (handle, event after their last use)
+
+    # A training step's forward state is a few device allocations (hundreds of
+    # megabytes at 100k Gaussians), which cost more than the step when made and
+    # freed every time (a 32-receiver step of one transmitter 4.5 ms, 0.9 ms of
+    # it on the GPU).  The autograd function's finished states are therefore
+    # kept for its next forwards: at most IDLE_MAX of them, never more than were
+    # in use together, and given back when an allocation fails, before work
+    # sized to the free memory (coverage maps, servers), and by
+    # release_idle_states() and close().
+    IDLE_MAX = 4
+
+    def _take_state(self) -> "Saved":
+        """A state whose buffers nothing uses any more, ordered after their last use."""
+        try:
+            h, ev = self._idle.pop()
+        except IndexError:
+            return Saved(self)
+        _torch().cuda.current_stream(self.device).wait_event(ev)
+        return Saved(self, h)
+
+    def _return_state(self, saved: "Saved"):
+        """Keep a state's buffers for a later forward (on any stream); the object itself is closed."""
+        if self._ctx is None or saved._h is None or len(self._idle) >= self.IDLE_MAX:
+            saved.close()
+            return
+        ev = _torch().cuda.Event()
+        ev.record(_torch().cuda.current_stream(self.device))
+        h, saved._h = saved._h, None
+        self._idle.append((h, ev))
+
+    def release_idle_states(self) -> int:
+        """Free the autograd function's kept forward states; returns how many there were."""
+        n = 0
+        while self._idle:
+            h, _ = self._idle.pop()
+            lib().rxgs_saved_destroy(h)
+            n += 1
+        return n
+
+    def _roomy(self, call):
+        """call(), and once more without the kept states if memory runs out."""
+        try:
+            return call()
+        except Exception as e:
+            oom = (isinstance(e, RxgsError) and e.status == 2) or isinstance(e, _torch().cuda.OutOfMemoryError)
+            if not oom or not self.release_idle_states():
+                raise
+        return call()
 
     def _stream(self):
         return c_void_p(_torch().cuda.current_stream(self.device).cuda_stream)
@@ -312,7 +362,8 @@ class Renderer:
         ts = [_dev_f32(x, self.device) for x in (means, log_scales, quats, logits, radiance, features)]
         K = int(ts[0].shape[0])
         self._scene_keep = ts
-        _check(lib().rxgs_scene_upload(self._ctx, K, *[_ptr(t) for t in ts], 1, self._stream()), self._ctx)
+        self._roomy(lambda: _check(lib().rxgs_scene_upload(self._ctx, K, *[_ptr(t) for t in ts], 1, self._stream()),
+                                   self._ctx))
         self.K = K
         self.use_mlp = features is not None
 
@@ -329,6 +380,9 @@ class Renderer:
                want_csum: bool = False, out=None, want_amp: bool = False):
         """Render receivers rx (N x 3).  Returns (C (N,2,H,W), power (N), csum or None), or with
         want_amp=True (C, power, csum or None, amplitude (N,H,W))."""
+        return self._roomy(lambda: self._render(rx, tx, rx_off, mode, saved, want_csum, out, want_amp))
+
+    def _render(self, rx, tx, rx_off, mode, saved, want_csum, out, want_amp):
         torch = _torch()
         rx_t = _dev_f32(rx, self.device).reshape(-1, 3)
         N = int(rx_t.shape[0])
@@ -375,14 +429,17 @@ class Renderer:
         if co.numel() != self.K * (int(model.lmax) + 1) ** 2 * int(model.C) * 2:
             raise ValueError("coefficients must be K x L x C x 2")
         self._rxc_keep = (co, pa)
-        _check(lib().rxgs_rxcond_upload(self._ctx, byref(self.rxc_desc), _ptr(co), _ptr(pa), 1, self._stream()),
-               self._ctx)
+        self._roomy(lambda: _check(lib().rxgs_rxcond_upload(self._ctx, byref(self.rxc_desc), _ptr(co), _ptr(pa), 1,
+                                                            self._stream()), self._ctx))
         self.rxc_C = int(model.C)
 
     def render_rxcond(self, rx, tx=None, rx_off=None, mode: str = "tx", saved: Saved | None = None,
                       want_csum: bool = False, want_amp: bool = False):
         """Render with the conditioned radiance (rxgs_render_rxcond): (C (N, Ch, 2, H, W),
         power (N, Ch), csum (N, Ch, 2) or None, amplitude (N, Ch, H, W) or None)."""
+        return self._roomy(lambda: self._render_rxcond(rx, tx, rx_off, mode, saved, want_csum, want_amp))
+
+    def _render_rxcond(self, rx, tx, rx_off, mode, saved, want_csum, want_amp):
         torch = _torch()
         rx_t = _dev_f32(rx, self.device).reshape(-1, 3)
         N = int(rx_t.shape[0])
@@ -424,6 +481,7 @@ class Renderer:
         """Coverage map: the receivers streamed through chunks whose workspace fits
         budget_bytes (0: half the free device memory).  Returns (C, power, chunks)."""
         torch = _torch()
+        self.release_idle_states()
         rx_t = _dev_f32(rx, self.device).reshape(-1, 3)
         N = int(rx_t.shape[0])
         if mode not in ("tx", "rx"):
@@ -471,8 +529,9 @@ class Renderer:
         dC_t = None if dC is None else dC.contiguous()
         dP_t = None if dP is None else _dev_f32(dP, dev)
         dA_t = None if dA is None else _dev_f32(dA, dev)
-        _check(lib().rxgs_render_backward(self._ctx, saved._h, _ptr(C.contiguous()), _ptr(dC_t), _ptr(dP_t),
-                                          _ptr(dA_t), byref(cg), self._stream()), self._ctx)
+        C_t = C.contiguous()
+        self._roomy(lambda: _check(lib().rxgs_render_backward(self._ctx, saved._h, _ptr(C_t), _ptr(dC_t), _ptr(dP_t),
+                                                              _ptr(dA_t), byref(cg), self._stream()), self._ctx))
         return grads
 
     def deterministic(self, on: bool = True):
@@ -515,6 +574,7 @@ class Renderer:
 
     def close(self):
         if getattr(self, "_ctx", None) is not None:
+            self.release_idle_states()
             lib().rxgs_destroy(self._ctx)
         self._ctx = None
 
@@ -547,6 +607,7 @@ class Server:
             if st != 0:
                 raise RxgsError(st, "host-executor server rejected its options")
         else:
+            renderer.release_idle_states()
             _check(lib().rxgs_server_start(renderer._ctx, byref(o), byref(h)), renderer._ctx)
         self._h = h
         self._n = {}
