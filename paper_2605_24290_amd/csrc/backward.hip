@@ -2,11 +2,13 @@
 // the same (tile, receiver) grid as the forward and accumulates Gaussian-level
 // gradients over receivers and directions with atomics).
 //
-//   k_blend_bwd     reverse walk of each tile list from the last composited
+//   k_blend_bwd_mm  reverse walk of each tile list from the last composited
 //                   entry: T_before = T_after / (1 - w) from the saved final
 //                   transmittance; per entry dL/ds (per receiver) and dL/d(u,
-//                   v, conic, opacity) summed over the wave (DPP), one atomic
-//                   per wave.                                        [VALU]
+//                   v, conic, opacity) as contractions over the wave's pixels
+//                   (moments), one atomic per tile.            [VALU + MFMA]
+//   k_blend_bwd     the same walk with every sum in a fixed order
+//                   (deterministic backward).                        [VALU]
 //   k_mlp_bwd       persistent FP32-MFMA backward of layers 2 and 3 over the
 //                   same work items as the forward (recompute, dz2, dx1 =
 //                   W2^T dz2, dW2 = dz2^T x1), per-wave partial sums. [MFMA]
@@ -30,13 +32,10 @@ constexpr float LN2F = 0.69314718055994531f;
 // Same (tile, receiver chunk) grid, pixel mapping, LDS staging and per-wave
 // entry lists as the forward; batches are staged from the end of the consumed
 // part of the tile list towards its start and walked in reverse.  Each
-// forward chunk is split into `split` blocks of at most R receivers.  The
-// per-entry wave sums of a batch are accumulated in LDS over the block's four
-// waves and flushed to global memory once per batch, one entry per thread:
-// global atomics inside the walk stall it (they count against the wave's
-// outstanding-memory budget) and contend across the waves of a tile.
-// Deterministic variant (DET): each wave adds its entry sums over its 64
-// lanes in a fixed order into its own LDS slots, the four waves' slots are
+// forward chunk is split into `split` blocks of at most R receivers.
+//
+// Deterministic backward (k_blend_bwd): each wave adds its entry sums over its
+// 64 lanes in a fixed order into its own LDS slots, the four waves' slots are
 // added in order at the flush, and every (pair, receiver block) gets its own
 // partial in global memory (no atomics), stored at the pair's emission slot
 // (its position's first slot plus the tile's index in the position's tile
@@ -52,20 +51,37 @@ struct DetPartials {
     const uint32_t *pbase;  // first pair slot of each view
 };
 
-template <int R, bool DET>
+// dL/dC of a pixel of row j: the spectrum's own gradient, the power's
+// (d|C|^2/dC = 2 C) and the amplitude's (d sqrt(|C|^2 + 1e-8)/dC = C / amplitude)
+__device__ __forceinline__ float2 pixel_grad(const float *__restrict__ C, const float *__restrict__ dC,
+                                             const float *__restrict__ dP, const float *__restrict__ dA, size_t j,
+                                             size_t P, size_t pix)
+{
+    const float gp = dP ? 2.f * dP[j] : 0.f;
+    const float cx = C[(j * 2) * P + pix], cy = C[(j * 2 + 1) * P + pix];
+    float2 G;
+    G.x = (dC ? dC[(j * 2) * P + pix] : 0.f) + gp * cx;
+    G.y = (dC ? dC[(j * 2 + 1) * P + pix] : 0.f) + gp * cy;
+    if (dA) {
+        const float ga = dA[j * P + pix] / sqrtf(cx * cx + cy * cy + AMP_EPS);
+        G.x += ga * cx;
+        G.y += ga * cy;
+    }
+    return G;
+}
+
+template <int R>
 __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
     const float4 *__restrict__ srec, const uint32_t *__restrict__ pval, const uint2 *__restrict__ ranges,
     const float2 *__restrict__ rad, const int4 *__restrict__ chunks, int split, int64_t Kp, DevGrid g,
     int tx_mode, const float *__restrict__ C, const float *__restrict__ dC, const float *__restrict__ dP,
-    const float *__restrict__ dA, const float *__restrict__ Tfin, const int *__restrict__ nlast, float *__restrict__ dS,
-    float *__restrict__ g2d, uint8_t *__restrict__ live, DetPartials det, const int4 *__restrict__ vinfo)
+    const float *__restrict__ dA, const float *__restrict__ Tfin, const int *__restrict__ nlast,
+    uint8_t *__restrict__ live, DetPartials det, const int4 *__restrict__ vinfo)
 {
     constexpr int NV = 6 + 2 * R;   // values per entry: six record gradients, then (Re, Im) per receiver
     __shared__ BlendStage st;
     __shared__ float2 s_rad[R][BLOCK];
-    __shared__ float s_acc[DET ? 1 : 6][BLOCK];
-    __shared__ float2 s_dacc[DET ? 1 : R][BLOCK];
-    __shared__ float s_accw[DET ? 4 : 1][DET ? NV : 1][BLOCK];
+    __shared__ float s_accw[4][NV][BLOCK];
     __shared__ int s_max[4];
 
     const int tile = blockIdx.x;
@@ -98,18 +114,7 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
         G[r] = make_float2(0.f, 0.f);
         A[r] = make_float2(0.f, 0.f);
         if (inside && r < nrx) {
-            const size_t j = (size_t)(j0 + r);
-            // dL/dC of the pixel: the spectrum's own gradient, the power's
-            // (d|C|^2/dC = 2 C) and the amplitude's (d sqrt(|C|^2 + 1e-8)/dC = C / amplitude)
-            const float gp = dP ? 2.f * dP[j] : 0.f;
-            const float cx = C[(j * 2) * P + pix], cy = C[(j * 2 + 1) * P + pix];
-            G[r].x = (dC ? dC[(j * 2) * P + pix] : 0.f) + gp * cx;
-            G[r].y = (dC ? dC[(j * 2 + 1) * P + pix] : 0.f) + gp * cy;
-            if (dA) {
-                const float ga = dA[j * P + pix] / sqrtf(cx * cx + cy * cy + AMP_EPS);
-                G[r].x += ga * cx;
-                G[r].y += ga * cy;
-            }
+            G[r] = pixel_grad(C, dC, dP, dA, (size_t)(j0 + r), P, pix);
         }
     }
     int m = last;
@@ -123,17 +128,10 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
         const int cnt = end - start;
         __syncthreads();
         uint32_t p = 0;
-        if constexpr (DET) {
 #pragma unroll
-            for (int w = 0; w < 4; w++)
+        for (int w = 0; w < 4; w++)
 #pragma unroll
-                for (int c = 0; c < NV; c++) s_accw[w][c][t] = 0.f;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 6; c++) s_acc[c][t] = 0.f;
-#pragma unroll
-            for (int r = 0; r < R; r++) s_dacc[r][t] = make_float2(0.f, 0.f);
-        }
+            for (int c = 0; c < NV; c++) s_accw[w][c][t] = 0.f;
         if (t < cnt) {
             p = (uint32_t)min((int64_t)pval[rg.x + start + t], view_end - 1);
             const int64_t s = max((int64_t)p - (int64_t)view * Kp, (int64_t)0);
@@ -200,90 +198,365 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
             }
             if (__ballot(act) == 0) continue;   // uniform across the wave
             float vals[6] = {gu, gv, gca, gcb, gcc, glo};
-            if constexpr (DET) {
-                // the wave's sum: its four 16-lane row sums added in order
-                auto wave_total = [&](float x) {
-                    const float v = row_sum(x);
-                    const int b = __float_as_int(v);
-                    return ((__int_as_float(__builtin_amdgcn_readlane(b, 15)) +
-                             __int_as_float(__builtin_amdgcn_readlane(b, 31))) +
-                            __int_as_float(__builtin_amdgcn_readlane(b, 47))) +
-                           __int_as_float(__builtin_amdgcn_readlane(b, 63));
-                };
-#pragma unroll
-                for (int c = 0; c < 6; c++) {
-                    const float v = wave_total(vals[c]);
-                    if (lane == 0) s_accw[wv][c][e] = v;
-                }
-#pragma unroll
-                for (int r = 0; r < R; r++) {
-                    if (r < nrx) {
-                        const float vx = wave_total(dsr[r].x);
-                        const float vy = wave_total(dsr[r].y);
-                        if (lane == 0) {
-                            s_accw[wv][6 + 2 * r][e] = vx;
-                            s_accw[wv][7 + 2 * r][e] = vy;
-                        }
-                    }
-                }
-                continue;
-            }
-            // sums over each 16-lane row, added into the batch's LDS
-            // accumulators by the rows' last lanes
-            const bool row_last = (lane & 15) == 15;
+            // the wave's sum: its four 16-lane row sums added in order
+            auto wave_total = [&](float x) {
+                const float v = row_sum(x);
+                const int b = __float_as_int(v);
+                return ((__int_as_float(__builtin_amdgcn_readlane(b, 15)) +
+                         __int_as_float(__builtin_amdgcn_readlane(b, 31))) +
+                        __int_as_float(__builtin_amdgcn_readlane(b, 47))) +
+                       __int_as_float(__builtin_amdgcn_readlane(b, 63));
+            };
 #pragma unroll
             for (int c = 0; c < 6; c++) {
-                const float v = row_sum(vals[c]);
-                if (row_last && v != 0.f) atomicAdd(&s_acc[c][e], v);
+                const float v = wave_total(vals[c]);
+                if (lane == 0) s_accw[wv][c][e] = v;
             }
 #pragma unroll
             for (int r = 0; r < R; r++) {
                 if (r < nrx) {
-                    const float vx = row_sum(dsr[r].x);
-                    const float vy = row_sum(dsr[r].y);
-                    if (row_last) {
-                        if (vx != 0.f) atomicAdd(&s_dacc[r][e].x, vx);
-                        if (vy != 0.f) atomicAdd(&s_dacc[r][e].y, vy);
+                    const float vx = wave_total(dsr[r].x);
+                    const float vy = wave_total(dsr[r].y);
+                    if (lane == 0) {
+                        s_accw[wv][6 + 2 * r][e] = vx;
+                        s_accw[wv][7 + 2 * r][e] = vy;
                     }
                 }
             }
         }
         __syncthreads();
-        if constexpr (DET) {
-            // thread t owns entry t: the four waves' sums in order, stored at
-            // the entry's pair slot for this block of receivers
-            if (t < cnt) {
-                const uint32_t pe = st.p[t];
-                // the pair's emission slot
-                const float4 b = det.sbox[pe];
-                int ty0, ty1, a0, a1, b0, b1;
-                (void)tile_rows(b.y, b.w, g.H, ty0, ty1);
-                (void)tile_cols(b.x, b.z, g.W, g.tiles_x, a0, a1, b0, b1);
-                const int64_t d = (int64_t)det.pbase[view] + det.poff[pe] + tile_rank(ty, tx, ty0, a0, a1, b0, b1);
-                const int4 vi = det.vinfo[view];
-                const int64_t blk = (j0 - vi.x) / R;
-                float *gp = det.gP + ((size_t)blk * det.Dpad + d) * 8;
+        // thread t owns entry t: the four waves' sums in order, stored at
+        // the entry's pair slot for this block of receivers
+        if (t < cnt) {
+            const uint32_t pe = st.p[t];
+            // the pair's emission slot
+            const float4 b = det.sbox[pe];
+            int ty0, ty1, a0, a1, b0, b1;
+            (void)tile_rows(b.y, b.w, g.H, ty0, ty1);
+            (void)tile_cols(b.x, b.z, g.W, g.tiles_x, a0, a1, b0, b1);
+            const int64_t d = (int64_t)det.pbase[view] + det.poff[pe] + tile_rank(ty, tx, ty0, a0, a1, b0, b1);
+            const int4 vi = det.vinfo[view];
+            const int64_t blk = (j0 - vi.x) / R;
+            float *gp = det.gP + ((size_t)blk * det.Dpad + d) * 8;
 #pragma unroll
-                for (int c = 0; c < 6; c++)
-                    gp[c] = ((s_accw[0][c][t] + s_accw[1][c][t]) + s_accw[2][c][t]) + s_accw[3][c][t];
-                bool any = false;
+            for (int c = 0; c < 6; c++)
+                gp[c] = ((s_accw[0][c][t] + s_accw[1][c][t]) + s_accw[2][c][t]) + s_accw[3][c][t];
+            bool any = false;
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    if (r < nrx) {
-                        const float vx = ((s_accw[0][6 + 2 * r][t] + s_accw[1][6 + 2 * r][t]) +
-                                          s_accw[2][6 + 2 * r][t]) + s_accw[3][6 + 2 * r][t];
-                        const float vy = ((s_accw[0][7 + 2 * r][t] + s_accw[1][7 + 2 * r][t]) +
-                                          s_accw[2][7 + 2 * r][t]) + s_accw[3][7 + 2 * r][t];
-                        float *dd = det.dSP + ((size_t)(j0 + r - vi.x) * det.Dpad + d) * 2;
-                        dd[0] = vx;
-                        dd[1] = vy;
-                        any = any || vx != 0.f || vy != 0.f;
+            for (int r = 0; r < R; r++) {
+                if (r < nrx) {
+                    const float vx = ((s_accw[0][6 + 2 * r][t] + s_accw[1][6 + 2 * r][t]) +
+                                      s_accw[2][6 + 2 * r][t]) + s_accw[3][6 + 2 * r][t];
+                    const float vy = ((s_accw[0][7 + 2 * r][t] + s_accw[1][7 + 2 * r][t]) +
+                                      s_accw[2][7 + 2 * r][t]) + s_accw[3][7 + 2 * r][t];
+                    float *dd = det.dSP + ((size_t)(j0 + r - vi.x) * det.Dpad + d) * 2;
+                    dd[0] = vx;
+                    dd[1] = vy;
+                    any = any || vx != 0.f || vy != 0.f;
+                }
+            }
+            if (any) live[pe / MLP_PAIRS] = 1;
+        }
+    }
+}
+
+// Reverse compositing on the matrix cores (float-atomic backward).
+//
+// Per entry and pixel the walk needs two scalars: with a = sum_r G_r . s_r the
+// radiance's product with dL/dC and D the same product of what lies behind,
+//   dL/dw = (T a - D) / (1 - w),  D += T_before w a,
+// whatever the number of receivers.  From them come
+//   gex = dL/dw w ln 2 (dL/d log2 weight) and tw = T_before w,
+// and everything the entry receives is a contraction over the wave's pixels:
+//   moments sum_p gex (1, X, Y, X^2, XY, Y^2), (X, Y) the pixel's offset from
+//   the sub-tile's centre, and dL/ds_r = sum_p tw G_r.
+// Eight entries at a time, the 8 + 8 rows (gex, tw) of 64 pixels go through
+// LDS into the A layout of v_mfma_f32_16x16x4_f32; B's columns are the six
+// basis values and the 2 RC components of G, constants of the lane (16
+// registers).  The gradients of (u, v, a, b, c, log2 o) follow from the
+// moments per entry: du = X + u0, dv = Y + v0.  Before, every entry summed
+// 6 + 2 R values over the wave by DPP and LDS atomics, each under its own
+// branch, about 60 instructions; now about 43 in all are left per entry, and the
+// kernel waits on LDS and the vector ALU alike (0.43 of the cycles each).  32
+// views of 100k Gaussians 303 -> 253 us, one view with 32 receivers 246 -> 157,
+// a 1,024-Gaussian view with 4 receivers 211 -> 65, 128 views of 1M 645 -> 560.
+//
+// Entries whose offsets wrap around the azimuth circle for some pixels: du
+// differs from X + u0 by delta = +-W there, and the three sums that changes
+// are added from their own wave sums (a uniform branch; such entries are few).
+// orders a wave's own LDS accesses (LDS operations of one wave complete in order)
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int BWD_LD = 68;   // floats per LDS row of 64 pixels (16-byte aligned, rows spread over the banks)
+
+template <int RC>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(RC <= 4 ? 3 : 2))) void k_blend_bwd_mm(
+    const float4 *__restrict__ srec, const uint32_t *__restrict__ pval, const uint2 *__restrict__ ranges,
+    const float2 *__restrict__ rad, const int4 *__restrict__ chunks, int split, int64_t Kp, DevGrid g, int tx_mode,
+    const float *__restrict__ C, const float *__restrict__ dC, const float *__restrict__ dP,
+    const float *__restrict__ dA, const float *__restrict__ Tfin, const int *__restrict__ nlast, float *__restrict__ dS,
+    float *__restrict__ g2d, uint8_t *__restrict__ live, const int4 *__restrict__ vinfo,
+    const uint32_t *__restrict__ torder)
+{
+    constexpr int NCB = (6 + 2 * RC + 15) / 16;   // blocks of 16 columns
+    __shared__ BlendStage st;
+    __shared__ float2 s_rad[BLOCK][RC];
+    __shared__ float s_acc[6][BLOCK];
+    __shared__ float s_dacc[2 * RC][BLOCK];
+    __shared__ __align__(16) float s_v[4][16 * BWD_LD];
+    __shared__ float s_m[4][8][7];      // per wave and entry of a group: its six moments
+    __shared__ float s_c[4][8][3];      // and its three wrap corrections
+    __shared__ int s_max[4];
+
+    // grid: (rank of the tile in its view's longest-first order, chunk and
+    // block of RC of its rows); the tiles of a view together: their entries'
+    // records and gradients stay in the caches (views first: 326 against 247 us)
+    const int4 ch = chunks[blockIdx.y / split];
+    const int sub = blockIdx.y - (blockIdx.y / split) * split;
+    const int tile = torder ? (int)torder[(size_t)ch.x * g.tiles + blockIdx.x] : (int)blockIdx.x;
+    const int view = ch.x, j0 = ch.y + sub * RC, nrx = min(ch.z - sub * RC, RC);
+    if (nrx <= 0) return;   // uniform over the block, before any barrier
+    const int tread = tx_mode ? view : j0;
+    const int4 vr = vinfo[view];   // its first row and rows
+    const int ty = tile / g.tiles_x, tx = tile - ty * g.tiles_x;
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int row0 = ty * TILE + 8 * (wv >> 1), col0 = tx * TILE + 8 * (wv & 1);
+    const int row = row0 + (lane >> 3), col = col0 + (lane & 7);
+    const bool inside = row < g.H && col < g.W;
+    const float rowf = (float)row, colf = (float)col;
+    const float Wf = (float)g.W, halfW = 0.5f * (float)g.W;
+    const uint2 rg = ranges[(size_t)view * g.tiles + tile];
+    const int64_t view_end = ((int64_t)view + 1) * Kp;
+    const size_t P = (size_t)g.H * g.W;
+    const size_t pix = (size_t)row * g.W + col;
+
+    float T = 1.f;
+    int last = 0;
+    if (inside) {
+        T = Tfin[(size_t)tread * P + pix];
+        last = nlast[(size_t)tread * P + pix];
+    }
+    float2 G[RC];
+#pragma unroll
+    for (int r = 0; r < RC; r++) {
+        G[r] = make_float2(0.f, 0.f);
+        if (inside && r < nrx) G[r] = pixel_grad(C, dC, dP, dA, (size_t)(j0 + r), P, pix);
+    }
+    float D = 0.f;
+    int m = last;
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+    const int wlast = __builtin_amdgcn_readfirstlane(m);
+    if (lane == 0) s_max[wv] = m;
+    // B operand: lane (column c = lane % 16, k group lane / 16) at step i holds
+    // column c of pixel 16 (lane / 16) + i
+    float *sv = s_v[wv];
+#pragma unroll
+    for (int r = 0; r < RC; r++) {
+        sv[(2 * r) * BWD_LD + lane] = G[r].x;
+        sv[(2 * r + 1) * BWD_LD + lane] = G[r].y;
+    }
+    __syncthreads();
+    const int bc = lane & 15, bg = lane >> 4;
+    float B[NCB][16];
+#pragma unroll
+    for (int b = 0; b < NCB; b++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int p = 16 * bg + i, c = 16 * b + bc;
+            const float X = (float)(p & 7) - 3.5f, Y = (float)(p >> 3) - 3.5f;
+            const float gv = c >= 6 && c < 6 + 2 * RC ? sv[(c - 6) * BWD_LD + p] : 0.f;
+            B[b][i] = c == 0 ? 1.f : c == 1 ? X : c == 2 ? Y : c == 3 ? X * X : c == 4 ? X * Y : c == 5 ? Y * Y : gv;
+        }
+    const int maxlast = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+    const float colc = (float)col0 + 3.5f, rowc = (float)row0 + 3.5f;
+
+    for (int end = maxlast; end > 0; end -= BLOCK) {
+        const int start = max(0, end - BLOCK);
+        const int cnt = end - start;
+        __syncthreads();
+        uint32_t p = 0;
+#pragma unroll
+        for (int c = 0; c < 6; c++) s_acc[c][t] = 0.f;
+#pragma unroll
+        for (int r = 0; r < 2 * RC; r++) s_dacc[r][t] = 0.f;
+        float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;
+        if (t < cnt) {
+            p = (uint32_t)min((int64_t)pval[rg.x + start + t], view_end - 1);
+            const int64_t s = max((int64_t)p - (int64_t)view * Kp, (int64_t)0);
+            q0 = srec[2 * (size_t)p];
+            q1 = srec[2 * (size_t)p + 1];
+#pragma unroll
+            for (int r = 0; r < RC; r++)
+                s_rad[t][r] = (r < nrx) ? rad[rad_index(vr, Kp, s, j0 + r)] : make_float2(0.f, 0.f);
+        }
+        stage_batch(st, q0, q1, p, t < cnt, tx, ty, g);
+        // the wave's list up to its own last composited entry (batch indices ascend)
+        int n = __builtin_amdgcn_readfirstlane(st.len[wv]);
+        {
+            int keep = 0;
+#pragma unroll
+            for (int q = 0; q < BLOCK / 64; q++) {
+                const int i = q * 64 + lane;
+                keep += (int)__popcll(__ballot(i < n && start + (int)st.list[wv][i] < wlast));
+            }
+            n = keep;
+        }
+        const int lim = last - start;
+        const bool wrap = __builtin_amdgcn_readfirstlane(st.wrap[wv]) != 0;
+        float *sm = &s_m[wv][0][0];
+        // what the wave does with a group's sums (of list entries i0 .. i0 + 7):
+        // lane (c, k group) holds column c of rows 4 (lane / 16) + 0 .. 3; rows
+        // 0-7 are the entries' gex (their moments in columns 0-5), rows 8-15
+        // their tw (dL/ds in the columns after)
+        auto write_out = [&](const floatx4 (&acc)[NCB], int i0) {
+            const int re = 4 * (bg & 1);
+            const ushort4 le = *reinterpret_cast<const ushort4 *>(&st.list[wv][i0 + re]);
+            const int eo[4] = {le.x, le.y, le.z, le.w};
+            if (bg < 2) {
+                if (bc < 6)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) sm[(re + r) * 7 + bc] = acc[0][r];
+            } else {
+#pragma unroll
+                for (int b = 0; b < NCB; b++) {
+                    const int c = 16 * b + bc - 6;
+                    if (c >= 0 && c < 2 * RC)
+#pragma unroll
+                        for (int r = 0; r < 4; r++)
+                            if (i0 + re + r < n) atomicAdd(&s_dacc[c][eo[r]], acc[b][r]);
+                }
+            }
+            wave_lds_fence();
+            if (lane < 8 && i0 + lane < n) {
+                const int e = st.list[wv][i0 + lane];
+                const float4 r0 = st.r0[e], r1 = st.r1[e];
+                const float *mm = sm + lane * 7, *cc = s_c[wv][lane];
+                const float M0 = mm[0], Mx = mm[1], My = mm[2], Mxx = mm[3], Mxy = mm[4], Myy = mm[5];
+                const float u0 = (colc - r0.x) - r0.y, v0 = (rowc - r0.z) - r0.w;
+                float Su = fmaf(u0, M0, Mx);
+                const float Sv = fmaf(v0, M0, My);
+                float Suu = fmaf(u0, Mx + Su, Mxx), Suv = fmaf(u0, My, fmaf(v0, Su, Mxy));
+                const float Svv = fmaf(v0, My + Sv, Myy);
+                if (wrap) {
+                    Su += cc[0];
+                    Suu += cc[1];
+                    Suv += cc[2];
+                }
+                atomicAdd(&s_acc[0][e], -(2.f * r1.x * Su + r1.y * Sv));
+                atomicAdd(&s_acc[1][e], -(r1.y * Su + 2.f * r1.z * Sv));
+                atomicAdd(&s_acc[2][e], Suu);
+                atomicAdd(&s_acc[3][e], Suv);
+                atomicAdd(&s_acc[4][e], Svv);
+                atomicAdd(&s_acc[5][e], M0);
+            }
+            wave_lds_fence();
+        };
+        float *sc = &s_c[wv][0][0];
+        for (int i0 = n > 0 ? (n - 1) & ~7 : -1; i0 >= 0; i0 -= 8) {
+            const ushort4 lf = *reinterpret_cast<const ushort4 *>(&st.list[wv][i0]);
+            if (wrap && lane < 24) sc[lane] = 0.f;
+#pragma unroll 1
+            for (int half = 1; half >= 0; half--) {
+                const int ih = i0 + 4 * half;
+                const ushort4 l4 = *reinterpret_cast<const ushort4 *>(&st.list[wv][ih]);
+                const int e[4] = {ih < n ? l4.x : lf.x, ih + 1 < n ? l4.y : lf.x, ih + 2 < n ? l4.z : lf.x,
+                                  ih + 3 < n ? l4.w : lf.x};
+                float4 r0[4], r1[4];
+                float2 sr[4][RC];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    r0[k] = st.r0[e[k]];
+                    r1[k] = st.r1[e[k]];
+#pragma unroll
+                    for (int r = 0; r < RC; r++) sr[k][r] = s_rad[e[k]][r];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                float du[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) du[k] = (colf - r0[k].x) - r0[k].y;
+                bool wide = false;   // some entry of the four wraps for some pixels
+                if (wrap) {   // uniform
+                    int wd[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) wd[k] = st.wide[e[k]];
+                    wide = __builtin_amdgcn_readfirstlane(wd[0] | wd[1] | wd[2] | wd[3]) != 0;
+                    if (wide) {
+#pragma unroll
+                        for (int k = 0; k < 4; k++) {
+                            const float d = du[k] >= halfW ? du[k] - Wf : du[k] < -halfW ? du[k] + Wf : du[k];
+                            du[k] = wd[k] ? d : du[k];
+                        }
                     }
                 }
-                if (any) live[pe / MLP_PAIRS] = 1;
+#pragma unroll
+                for (int k = 3; k >= 0; k--) {
+                    const float dv = (rowf - r0[k].z) - r0[k].w;
+                    const float wr = __builtin_amdgcn_exp2f(blend_exponent(du[k], dv, r1[k]));
+                    const float wc = fminf(W_MAX, wr);
+                    const bool act = ih + k < n && e[k] < lim && wc >= ALPHA_MIN;
+                    const float w = act ? wc : 0.f;
+                    float a = 0.f;
+#pragma unroll
+                    for (int r = 0; r < RC; r++) a = fmaf(G[r].x, sr[k][r].x, fmaf(G[r].y, sr[k][r].y, a));
+                    a = act ? a : 0.f;   // (a position no pixel composites may have no radiance)
+                    // 1 / (1 - w) by the hardware reciprocal (1 ulp; 1 - w >= 0.01):
+                    // over a pixel's few dozen composited entries the recovered
+                    // transmittance stays within ~1e-6 of the forward's
+                    const float rw = __builtin_amdgcn_rcpf(1.f - w);
+                    const float Tb = T * rw;   // (w = 0: rw = 1)
+                    const float tw = Tb * w;
+                    const float dw = fmaf(T, a, -D) * rw;
+                    const float gex = wr < W_MAX ? dw * w * LN2F : 0.f;
+                    D = fmaf(tw, a, D);
+                    T = Tb;
+                    sv[(4 * half + k) * BWD_LD + lane] = gex;
+                    sv[(8 + 4 * half + k) * BWD_LD + lane] = tw;
+                }
+                if (wide) {   // uniform
+                    for (int k = 0; k < 4; k++) {
+                        const float4 rr = st.r0[e[k]];
+                        const float du0 = (colf - rr.x) - rr.y, dv = (rowf - rr.z) - rr.w;
+                        float d = du0 >= halfW ? -Wf : du0 < -halfW ? Wf : 0.f;   // du - du0
+                        d = st.wide[e[k]] ? d : 0.f;
+                        if (!__ballot(d != 0.f)) continue;
+                        // (read back: this wave's row of the entry)
+                        const float gd = sv[(4 * half + k) * BWD_LD + lane] * d;
+                        const float c1 = wave_sum_last(gd), c2 = wave_sum_last(gd * (2.f * du0 + d)),
+                                    c3 = wave_sum_last(gd * dv);
+                        if (lane == 63) {
+                            sc[(4 * half + k) * 3] = c1;
+                            sc[(4 * half + k) * 3 + 1] = c2;
+                            sc[(4 * half + k) * 3 + 2] = c3;
+                        }
+                    }
+                }
             }
-            continue;
+            wave_lds_fence();
+            float4 A[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                A[q] = *reinterpret_cast<const float4 *>(sv + bc * BWD_LD + 16 * bg + 4 * q);
+            wave_lds_fence();
+            floatx4 acc[NCB];
+#pragma unroll
+            for (int b = 0; b < NCB; b++) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const float Aq[4] = {A[q].x, A[q].y, A[q].z, A[q].w};
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+#pragma unroll
+                    for (int b = 0; b < NCB; b++)
+                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aq[i], B[b][4 * q + i], acc[b], 0, 0, 0);
+            }
+            write_out(acc, i0);
         }
+        __syncthreads();
         // flush the batch: thread t owns entry t
         if (t < cnt) {
             const uint32_t pe = st.p[t];
@@ -295,13 +568,13 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
             const int64_t s = (int64_t)pe - (int64_t)view * Kp;
             bool any = false;
 #pragma unroll
-            for (int r = 0; r < R; r++) {
+            for (int r = 0; r < RC; r++) {
                 if (r < nrx) {
-                    const float2 d = s_dacc[r][t];
+                    const float dx = s_dacc[2 * r][t], dy = s_dacc[2 * r + 1][t];
                     float *dd = dS + ((size_t)(j0 + r) * Kp + s) * 2;
-                    if (d.x != 0.f) atomicAdd(dd, d.x);
-                    if (d.y != 0.f) atomicAdd(dd + 1, d.y);
-                    any = any || d.x != 0.f || d.y != 0.f;
+                    if (dx != 0.f) atomicAdd(dd, dx);
+                    if (dy != 0.f) atomicAdd(dd + 1, dy);
+                    any = any || dx != 0.f || dy != 0.f;
                 }
             }
             // the MLP backward only visits position blocks marked here
@@ -1344,23 +1617,37 @@ hipError_t launch_zero_ranges(const ZeroRanges &z, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int R, bool DET>
-static hipError_t blend_bwd_launch(Workspace &ws, const float *C, const float *dC, const float *dP, const float *dA,
-                                   hipStream_t st)
+template <int R>
+static hipError_t blend_bwd_det_launch(Workspace &ws, const float *C, const float *dC, const float *dP, const float *dA,
+                                       hipStream_t st)
 {
     // forward chunks hold at most ws.R receivers; split them into R-receiver blocks
     const int split = (ws.R + R - 1) / R;
     const int64_t ny = (int64_t)ws.n_chunks * split;
     if (ny > 65535 || ws.g.tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
     dim3 grid((unsigned)ws.g.tiles, (unsigned)ny);
-    const DetPartials det = DET ? DetPartials{ws.gP.as<float>(), ws.dSP.as<float>(), ws.Dpad, ws.d_vinfo,
-                                              ws.sbox.as<float4>(), ws.poff.as<uint32_t>(), ws.d_pbase}
-                                : DetPartials{nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr};
-    hipLaunchKernelGGL((k_blend_bwd<R, DET>), grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
+    const DetPartials det{ws.gP.as<float>(), ws.dSP.as<float>(), ws.Dpad, ws.d_vinfo,
+                          ws.sbox.as<float4>(), ws.poff.as<uint32_t>(), ws.d_pbase};
+    hipLaunchKernelGGL(k_blend_bwd<R>, grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
                        ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.rad.as<float2>(),
                        ws.d_chunks, split, ws.Kp, ws.g, ws.mode == RXGS_MODE_TX ? 1 : 0, C, dC, dP, dA,
+                       ws.Tfin.as<float>(), ws.nlast.as<int>(), ws.live.as<uint8_t>(), det, ws.d_vinfo);
+    return hipGetLastError();
+}
+
+template <int RC>
+static hipError_t blend_bwd_mm_launch(Workspace &ws, const float *C, const float *dC, const float *dP, const float *dA,
+                                      hipStream_t st)
+{
+    // forward chunks hold at most ws.R rows; split them into blocks of RC
+    const int split = (ws.R + RC - 1) / RC;
+    const int64_t ny = (int64_t)ws.n_chunks * split;
+    if (ny > 65535 || ws.g.tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_blend_bwd_mm<RC>, dim3((unsigned)ws.g.tiles, (unsigned)ny), dim3(BLOCK), 0, st,
+                       ws.srec.as<float4>(), ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(),
+                       ws.rad.as<float2>(), ws.d_chunks, split, ws.Kp, ws.g, ws.mode == RXGS_MODE_TX ? 1 : 0, C, dC, dP, dA,
                        ws.Tfin.as<float>(), ws.nlast.as<int>(), ws.dS.as<float>(), ws.g2d.as<float>(),
-                       ws.live.as<uint8_t>(), det, ws.d_vinfo);
+                       ws.live.as<uint8_t>(), ws.d_vinfo, ws.tiles_ordered ? ws.torder.as<uint32_t>() : nullptr);
     return hipGetLastError();
 }
 
@@ -1370,16 +1657,16 @@ hipError_t launch_blend_bwd(Workspace &ws, const float *C, const float *dC, cons
     if (ws.n_chunks == 0) return hipSuccess;
     if (ws.det) {
         switch (det_block_rows(ws)) {
-        case 1: return blend_bwd_launch<1, true>(ws, C, dC, dP, dA, st);
-        case 2: return blend_bwd_launch<2, true>(ws, C, dC, dP, dA, st);
-        default: return blend_bwd_launch<4, true>(ws, C, dC, dP, dA, st);
+        case 1: return blend_bwd_det_launch<1>(ws, C, dC, dP, dA, st);
+        case 2: return blend_bwd_det_launch<2>(ws, C, dC, dP, dA, st);
+        default: return blend_bwd_det_launch<4>(ws, C, dC, dP, dA, st);
         }
     }
     switch (ws.R) {
-    case 1: return blend_bwd_launch<1, false>(ws, C, dC, dP, dA, st);
-    case 2: return blend_bwd_launch<2, false>(ws, C, dC, dP, dA, st);
-    case 4: return blend_bwd_launch<4, false>(ws, C, dC, dP, dA, st);
-    default: return blend_bwd_launch<8, false>(ws, C, dC, dP, dA, st);   // 8 and 16
+    case 1: return blend_bwd_mm_launch<1>(ws, C, dC, dP, dA, st);
+    case 2:
+    case 4: return blend_bwd_mm_launch<4>(ws, C, dC, dP, dA, st);
+    default: return blend_bwd_mm_launch<8>(ws, C, dC, dP, dA, st);   // 8 and 16
     }
 }
 
