@@ -14,15 +14,16 @@ __device__ __forceinline__ int count_below(uint64_t m)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Lanes of a wave whose 8-bit keys equal this lane's, among the lanes in
-// `m`: eight ballots, one per key bit; a lane keeps the lanes whose bit
+// Lanes of a wave whose BITS-bit keys equal this lane's, among the lanes in
+// `m`: a ballot per key bit; a lane keeps the lanes whose bit
 // agrees with its own (m & (bb xnor own bit), one three-input bit operation
 // per 32-lane half; truth table 0x90 over (m, bb, own bit)).
-__device__ __forceinline__ uint64_t match_key8(uint32_t d, uint64_t m)
+template <int BITS = 8>
+__device__ __forceinline__ uint64_t match_key(uint32_t d, uint64_t m)
 {
     uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
 #pragma unroll
-    for (int bt = 0; bt < 8; bt++) {
+    for (int bt = 0; bt < BITS; bt++) {
         const uint32_t own = (uint32_t)(((int32_t)(d << (31 - bt))) >> 31);   // all ones if bit bt is set
         const uint64_t bb = __ballot(own != 0u);
         lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bb, own, 0x90);

@@ -13,7 +13,7 @@
 //                  depth order; visible ones compacted into blend
 //                  records, boxes and pair offsets; per chunk its pairs
 //                  per tile.                                        [ALU]
-//   k_bin_scan,    grids of at most 255 tiles: each chunk's start in every
+//   k_bin_scan,    grids of at most 1,024 tiles: each chunk's start in every
 //   k_bin_pairs    tile list, then each (tile, sorted position) pair placed
 //                  directly in its tile list, in depth order.       [ALU]
 //   k_emit2 and    larger grids: the pairs emitted in depth order into the
@@ -447,12 +447,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
     const uint32_t *__restrict__ order, const uint32_t *__restrict__ kept, int cpv,
     float4 *__restrict__ srec, float4 *__restrict__ sbox, uint32_t *__restrict__ vorder, uint32_t *__restrict__ poff,
     unsigned long long *__restrict__ counters, unsigned long long *status, uint32_t *err,
-    uint32_t limit, uint32_t *__restrict__ vflag, uint32_t *__restrict__ bcnt, uint4 *__restrict__ binfo)
+    uint32_t limit, uint32_t *__restrict__ vflag, uint32_t *__restrict__ bcnt, int bstride,
+    uint4 *__restrict__ binfo)
 {
     constexpr int NW = NT / 64;
     __shared__ uint2 s_w2[NW];
     __shared__ uint32_t s_vbase, s_pbase;
-    __shared__ int s_d[BIN_DIFF_WORDS];
+    extern __shared__ int s_d[];   // per-tile difference counts, tiles_y x (tiles_x + 1) (with bcnt only)
     constexpr int EM1_CHUNK = NT * EM1_PER;
     const int t = threadIdx.x;
     const uint32_t nviews = gridDim.x / (unsigned)cpv;
@@ -574,12 +575,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
         }
     }
     __syncthreads();
-    if (bcnt && t < g.tiles) {
-        const int ty = t / g.tiles_x, tx = t - ty * g.tiles_x;
-        int c = 0;
-        for (int x = 0; x <= tx; x++) c += s_d[ty * dw + x];
-        bcnt[((size_t)v * cpv + chunk) * 256 + t] = (uint32_t)c;
-    }
+    if (bcnt)
+        for (int tl = t; tl < g.tiles; tl += NT) {
+            const int ty = tl / g.tiles_x, tx = tl - ty * g.tiles_x;
+            int c = 0;
+            for (int x = 0; x <= tx; x++) c += s_d[ty * dw + x];
+            bcnt[((size_t)v * cpv + chunk) * bstride + tl] = (uint32_t)c;
+        }
     size_t q = (size_t)v * Kp + s_vbase + pre.x;
     uint32_t po = s_pbase + pre.y;
 #pragma unroll
@@ -726,20 +728,28 @@ __global__ __launch_bounds__(BLOCK) void k_emit2(const float4 *__restrict__ sbox
 // tiles, a chunk's pairs of that tile follow the earlier chunks', and a
 // unit's follow the chunk's slots before the unit.  Inside a unit the pairs
 // keep slot order (an entry covers a tile at most once, so this is depth
-// order).  The result is the stable sort of the emitted pairs by tile.
+// order).  The result is the stable sort of the emitted pairs by tile.  Grids
+// of up to 1,024 tiles (the tables' LDS and the counts' 4 bytes per tile and
+// chunk grow with them): 17 views of 50k Gaussians on 276 tiles rendered in 443
+// us with the pair sort (emission 56 us, sort 64, ranges 20, clears 9) and take
+// 324 this way (49 us).
 //
-// One workgroup per view.  Per tile (one thread each): each live chunk's
-// count becomes the count of the view's earlier chunks (chunks read
-// BIN_SCAN_WIDE, then BIN_SCAN_BATCH at a time, all in flight together) and
-// the total is the tile's list length.  Per live chunk: the index of its first group of
-// units (up to `group` units, one workgroup of k_bin_pairs) within the view
-// (exclusive prefix, nlive + 1 words).
-constexpr int BIN_SCAN_BATCH = 16, BIN_SCAN_WIDE = 64;
-
+// Grid (view, slice of BIN_SLICE of its chunks, group of 256 tiles), one tile
+// per thread: each live chunk's count becomes the count of the view's earlier
+// chunks (a slice's chunks read all in flight together) and the total is the
+// tile's list length.  Views of more than one slice take two launches: the
+// slices' sums (SUMS) and then the starts, each slice adding the sums of those
+// before it; one workgroup walking all of a view's chunks took 195 us on a view
+// of 1M Gaussians (3,900 chunks; 980 since), the two launches take 12.  The first
+// slice also leaves, per live chunk, the index of its first group of units (up
+// to `group` units, one workgroup of k_bin_pairs) within the view (exclusive
+// prefix, nlive + 1 words).
+template <bool SUMS>
 __global__ __launch_bounds__(BLOCK) void k_bin_scan(const uint32_t *__restrict__ hist, int passes, uint32_t limit,
-                                                    int cpv, int chunk, int tiles, int group,
+                                                    int cpv, int chunk, int tiles, int bstride, int group,
                                                     const uint4 *__restrict__ binfo,
-                                                    uint32_t *__restrict__ bcnt, uint32_t *__restrict__ btot,
+                                                    uint32_t *__restrict__ bcnt, uint32_t *__restrict__ bsum,
+                                                    uint32_t *__restrict__ btot,
                                                     uint32_t *__restrict__ blive, uint32_t *__restrict__ bunit)
 {
     __shared__ uint32_t s_w[4];
@@ -748,45 +758,56 @@ __global__ __launch_bounds__(BLOCK) void k_bin_scan(const uint32_t *__restrict__
     uint32_t kept;
     (void)block_exclusive_scan(hist[((size_t)v * passes) * 256 + t], kept, s_w);
     const uint32_t nlive = (min(kept, limit) + (uint32_t)chunk - 1) / (uint32_t)chunk;
-    if (t == 0) blive[v] = nlive;
-    uint32_t *wp = bunit + (size_t)v * (cpv + 1);
-    uint32_t ubase = 0;
-    for (uint32_t j0 = 0; j0 < nlive; j0 += BLOCK) {   // uniform
-        const uint32_t j = j0 + t;
-        const uint32_t n = j < nlive ? (binfo[(size_t)v * cpv + j].w + BIN_WIN * group - 1) / (BIN_WIN * group)
-                                     : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_exclusive_scan(n, tot, s_w);
-        if (j < nlive) wp[j] = ubase + ex;
-        ubase += tot;
+    const uint32_t slice = blockIdx.y, c0 = slice * BIN_SLICE, c1 = min(nlive, c0 + BIN_SLICE);
+    if (!SUMS && slice == 0 && blockIdx.z == 0) {
+        if (t == 0) blive[v] = nlive;
+        uint32_t *wp = bunit + (size_t)v * (cpv + 1);
+        uint32_t ubase = 0;
+        for (uint32_t j0 = 0; j0 < nlive; j0 += BLOCK) {   // uniform
+            const uint32_t j = j0 + t;
+            const uint32_t n = j < nlive ? (binfo[(size_t)v * cpv + j].w + BIN_WIN * group - 1) / (BIN_WIN * group)
+                                         : 0u;
+            uint32_t tot;
+            const uint32_t ex = block_exclusive_scan(n, tot, s_w);
+            if (j < nlive) wp[j] = ubase + ex;
+            ubase += tot;
+        }
+        if (t == 0) wp[nlive] = ubase;
     }
-    if (t == 0) wp[nlive] = ubase;
-    if (t >= tiles) return;
+    const int tl = (int)blockIdx.z * BLOCK + t;
+    if (tl >= tiles) return;
+    // (a view without live chunks: empty lists, from its first slice)
+    if (c0 >= c1 && (SUMS || slice != 0)) return;
+    uint32_t *col = bcnt + ((size_t)v * cpv + c0) * bstride + tl;
+    const uint32_t n = c1 > c0 ? c1 - c0 : 0u;
+    uint32_t *sums = bsum + (size_t)v * gridDim.y * bstride + tl;
     uint32_t run = 0;
-    uint32_t *col = bcnt + (size_t)v * cpv * 256 + t;
-    uint32_t j0 = 0;
-    // whole batches of BIN_SCAN_WIDE chunks (no per-chunk bound tests), then the rest
-    for (; j0 + BIN_SCAN_WIDE <= nlive; j0 += BIN_SCAN_WIDE) {
-        uint32_t c[BIN_SCAN_WIDE];
+    if (!SUMS)
+        for (uint32_t q = 0; q < slice; q++) run += sums[(size_t)q * bstride];
+    if (n == BIN_SLICE) {   // a whole slice: no per-chunk bound tests
+        uint32_t c[BIN_SLICE];
 #pragma unroll
-        for (int q = 0; q < BIN_SCAN_WIDE; q++) c[q] = col[(size_t)(j0 + q) * 256];
+        for (int q = 0; q < BIN_SLICE; q++) c[q] = col[(size_t)q * bstride];
 #pragma unroll
-        for (int q = 0; q < BIN_SCAN_WIDE; q++) {
-            col[(size_t)(j0 + q) * 256] = run;
+        for (int q = 0; q < BIN_SLICE; q++) {
+            if (!SUMS) col[(size_t)q * bstride] = run;
             run += c[q];
         }
-    }
-    for (; j0 < nlive; j0 += BIN_SCAN_BATCH) {
-        uint32_t c[BIN_SCAN_BATCH];
+    } else {
+        constexpr int BATCH = 16;
+        for (uint32_t j0 = 0; j0 < n; j0 += BATCH) {
+            uint32_t c[BATCH];
 #pragma unroll
-        for (int q = 0; q < BIN_SCAN_BATCH; q++) c[q] = j0 + q < nlive ? col[(size_t)(j0 + q) * 256] : 0u;
+            for (int q = 0; q < BATCH; q++) c[q] = j0 + q < n ? col[(size_t)(j0 + q) * bstride] : 0u;
 #pragma unroll
-        for (int q = 0; q < BIN_SCAN_BATCH; q++) {
-            if (j0 + q < nlive) col[(size_t)(j0 + q) * 256] = run;
-            run += c[q];
+            for (int q = 0; q < BATCH; q++) {
+                if (!SUMS && j0 + q < n) col[(size_t)(j0 + q) * bstride] = run;
+                run += c[q];
+            }
         }
     }
-    btot[(size_t)v * 256 + t] = run;
+    if (SUMS) sums[(size_t)slice * bstride] = run;
+    else if (c1 == nlive) btot[(size_t)v * bstride + tl] = run;
 }
 
 // +1 / -1 at the ends of the column runs [a0, a1] and [b0, b1] of tile row ty
@@ -811,10 +832,13 @@ __device__ __forceinline__ void bin_diff_row(int *s_d, int dw, int ty, int a0, i
 // are marked in a bitmap of its slots, and each wave takes a contiguous part
 // of the unit 64 slots at a time: a slot's entry is the
 // number of marks up to it, its tile follows from its rank inside that
-// entry's rectangle; the wave ranks its slots by tile (match_key8 and a
+// entry's rectangle; the wave ranks its slots by tile (match_key and a
 // per-wave count per tile in LDS), and the waves' counts give each wave its
 // start in every tile's list; the unit's counts advance the starts for the
 // next unit.
+// TPT (1, 2 or 4): tiles per thread, 256 x TPT cover the grid; a unit's slots
+// are matched by 8, 9 or 10 key bits.
+template <int TPT>
 __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ sbox,
                                                      const uint32_t *__restrict__ poff, int64_t Kp, DevGrid g,
                                                      int cpv, int V, int group, const uint32_t *__restrict__ uoff,
@@ -830,8 +854,9 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
     __shared__ uint32_t s_rect[BIN_CHUNK_MAX];    // per entry of the units: ty0, a0, columns in range a, columns
     __shared__ uint32_t s_mark[BIN_WIN / 32];     // slots of the unit where an entry after the first starts
     __shared__ uint32_t s_mpre[BIN_WIN / 32];     // marks in the words before each word
-    __shared__ int s_d[BIN_DIFF_WORDS];           // difference counts of the chunk's slots before the unit
-    __shared__ uint32_t s_wc[4][256];             // per wave: its pairs per tile, then its start in each list
+    constexpr int BINS = 256 * TPT, BITS = TPT == 1 ? 8 : TPT == 2 ? 9 : 10;
+    extern __shared__ int s_d[];                  // difference counts of the chunk's slots before the unit
+    __shared__ uint32_t s_wc[4][BINS];            // per wave: its pairs per tile, then its start in each list
     __shared__ uint32_t s_w[4];
     __shared__ uint32_t s_probe, s_j, s_ea, s_eb, s_ej;
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
@@ -861,8 +886,6 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
         if (wp[c] <= u && u < wp[c + 1]) s_j = c;
     const int dw = g.tiles_x + 1;
     for (int i = t; i < g.tiles_y * dw; i += BLOCK) s_d[i] = 0;
-#pragma unroll
-    for (int ww = 0; ww < 4; ww++) s_wc[ww][t] = 0;
     __syncthreads();
     const uint32_t j = s_j;
     const uint4 bi = binfo[(size_t)v * cpv + j];
@@ -913,19 +936,30 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
         }
         s_rect[e] = (uint32_t)ty0 | ((uint32_t)a0 << 8) | ((uint32_t)na << 16) | ((uint32_t)nc << 24);
     }
-    // start of each tile's run for the first unit (the scan's barriers also
-    // order the tables above before their reads)
-    uint32_t start;
+    // start of each tile's run for the first unit, of the thread's TPT
+    // consecutive tiles (the scan's barriers also order the tables above before
+    // their reads)
+    uint32_t start[TPT];
     {
-        const uint32_t c = t < g.tiles ? btot[(size_t)v * 256 + t] : 0u;
+        uint32_t c[TPT], sum = 0;
+#pragma unroll
+        for (int q = 0; q < TPT; q++) {
+            c[q] = t * TPT + q < g.tiles ? btot[(size_t)v * BINS + t * TPT + q] : 0u;
+            sum += c[q];
+        }
         uint32_t total;
-        const uint32_t ex = block_exclusive_scan(c, total, s_w);
-        start = pbase[v] + ex;
-        if (t < g.tiles) {
-            const int ty = t / g.tiles_x, tx = t - ty * g.tiles_x;
-            int before = 0;
-            for (int x = 0; x <= tx; x++) before += s_d[ty * dw + x];
-            start += bcnt[((size_t)v * cpv + j) * 256 + t] + (uint32_t)before;
+        uint32_t ex = pbase[v] + block_exclusive_scan(sum, total, s_w);
+#pragma unroll
+        for (int q = 0; q < TPT; q++) {
+            const int tl = t * TPT + q;
+            start[q] = ex;
+            ex += c[q];
+            if (tl < g.tiles) {
+                const int ty = tl / g.tiles_x, tx = tl - ty * g.tiles_x;
+                int before = 0;
+                for (int x = 0; x <= tx; x++) before += s_d[ty * dw + x];
+                start[q] += bcnt[((size_t)v * cpv + j) * BINS + tl] + (uint32_t)before;
+            }
         }
     }
     const uint32_t seg_end = pbase[v] + pcount[v];
@@ -935,7 +969,9 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
         __syncthreads();
         if (t < BIN_WIN / 32) s_mark[t] = 0;
 #pragma unroll
-        for (int ww = 0; ww < 4; ww++) s_wc[ww][t] = 0;
+        for (int ww = 0; ww < 4; ww++)
+#pragma unroll
+            for (int q = 0; q < TPT; q++) s_wc[ww][q * BLOCK + t] = 0;
         __syncthreads();
         // the entry holding slot s0, and a mark where each later entry starts
         for (uint32_t e = ea + t; e <= eb; e += BLOCK) {
@@ -992,20 +1028,22 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
                 key[r] = d;
                 val[r] = (uint32_t)(row + e);
             }
-            const uint64_t m = match_key8(d, __ballot(valid));
+            const uint64_t m = match_key<BITS>(d, __ballot(valid));
             const uint32_t below = (uint32_t)count_below(m);
             const uint32_t before = valid ? s_wc[w][d] : 0u;
             rk[r] = before + below;
             if (valid && below == 0) s_wc[w][d] = before + (uint32_t)__popcll(m);
         }
         __syncthreads();
-        {
-            const uint32_t c0w = s_wc[0][t], c1w = s_wc[1][t], c2w = s_wc[2][t], c3w = s_wc[3][t];
-            s_wc[0][t] = start;
-            s_wc[1][t] = start + c0w;
-            s_wc[2][t] = start + c0w + c1w;
-            s_wc[3][t] = start + c0w + c1w + c2w;
-            start += c0w + c1w + c2w + c3w;   // the next unit's start
+#pragma unroll
+        for (int q = 0; q < TPT; q++) {
+            const int tl = t * TPT + q;
+            const uint32_t c0w = s_wc[0][tl], c1w = s_wc[1][tl], c2w = s_wc[2][tl], c3w = s_wc[3][tl];
+            s_wc[0][tl] = start[q];
+            s_wc[1][tl] = start[q] + c0w;
+            s_wc[2][tl] = start[q] + c0w + c1w;
+            s_wc[3][tl] = start[q] + c0w + c1w + c2w;
+            start[q] += c0w + c1w + c2w + c3w;   // the next unit's start
         }
         __syncthreads();
 #pragma unroll
@@ -1026,25 +1064,34 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
 // lists of every view first, which shortens the tail of its grid.
 __device__ __forceinline__ void ranges_of_view(int v, const uint32_t *__restrict__ hist,
                                                const uint32_t *__restrict__ pbase,
-                                               const uint32_t *__restrict__ pcount, int tiles,
+                                               const uint32_t *__restrict__ pcount, int tiles, int tpt,
                                                uint2 *__restrict__ ranges, uint32_t *__restrict__ torder)
 {
     __shared__ uint32_t s_w[4];
-    __shared__ uint32_t s_c[BLOCK];
+    __shared__ uint32_t s_c[BIN_MAX_TILES];
     const int t = threadIdx.x;
-    const uint32_t c = pcount[v] ? hist[(size_t)v * 256 + t] : 0u;
-    s_c[t] = c;
+    // tpt consecutive tiles per thread
+    uint32_t sum = 0;
+    for (int q = 0; q < tpt; q++) {
+        const int tl = t * tpt + q;
+        const uint32_t c = pcount[v] && tl < tiles ? hist[(size_t)v * (256 * tpt) + tl] : 0u;
+        s_c[tl] = c;
+        sum += c;
+    }
     uint32_t tot;
-    const uint32_t ex = block_exclusive_scan(c, tot, s_w);
-    if (t < tiles) {
-        const uint32_t s0 = pbase[v] + ex;
-        ranges[(size_t)v * tiles + t] = c ? make_uint2(s0, s0 + c) : make_uint2(0u, 0u);
+    uint32_t s0 = pbase[v] + block_exclusive_scan(sum, tot, s_w);
+    for (int q = 0; q < tpt; q++) {
+        const int tl = t * tpt + q;
+        if (tl >= tiles) break;
+        const uint32_t c = s_c[tl];
+        ranges[(size_t)v * tiles + tl] = c ? make_uint2(s0, s0 + c) : make_uint2(0u, 0u);
+        s0 += c;
         int rank = 0;
         for (int u = 0; u < tiles; u++) {
             const uint32_t cu = s_c[u];
-            rank += (cu > c || (cu == c && u < t)) ? 1 : 0;
+            rank += (cu > c || (cu == c && u < tl)) ? 1 : 0;
         }
-        torder[(size_t)v * tiles + rank] = (uint32_t)t;
+        torder[(size_t)v * tiles + rank] = (uint32_t)tl;
     }
 }
 
@@ -1169,7 +1216,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_global(const float *__restrict__ 
 // items (the workgroups after them) in one launch; also clears a buffer.
 __global__ __launch_bounds__(BLOCK) void k_ranges_items(const uint32_t *__restrict__ hist,
                                                         const uint32_t *__restrict__ pbase,
-                                                        const uint32_t *__restrict__ pcount, int tiles,
+                                                        const uint32_t *__restrict__ pcount, int tiles, int tpt,
                                                         uint2 *__restrict__ ranges, uint32_t *__restrict__ torder,
                                                         const uint32_t *__restrict__ item_off,
                                                         const int4 *__restrict__ vinfo, int V, int nitems,
@@ -1179,7 +1226,7 @@ __global__ __launch_bounds__(BLOCK) void k_ranges_items(const uint32_t *__restri
     // clears z (the position-block marks of the radiance prefix path)
     for (size_t k = (size_t)blockIdx.x * BLOCK + threadIdx.x; k < nz; k += (size_t)gridDim.x * BLOCK) z[k] = 0u;
     if ((int)blockIdx.x < V) {
-        ranges_of_view(blockIdx.x, hist, pbase, pcount, tiles, ranges, torder);
+        ranges_of_view(blockIdx.x, hist, pbase, pcount, tiles, tpt, ranges, torder);
         return;
     }
     const int i = ((int)blockIdx.x - V) * BLOCK + threadIdx.x;
@@ -2641,11 +2688,14 @@ size_t emit_word_count(int V, int64_t Kp)
 
 // chunks of 1024 entries (512 threads, 2 per thread) when there are many,
 // which amortises each chunk's look-back; 256 (1 per thread) for small
-// launches, which keeps the chain of chunks short
+// launches, which keeps the chain of chunks short.  The line is two workgroups
+// of 512 per CU: renders of 512 to 1,024 wide chunks are 2-4% faster with them
+// (12 views x 50k 288 -> 280 us, one view of 900k 394 -> 383), 512 of 9,000
+// kept entries' views are as fast either way.
 void emit1_chunking(Workspace &ws)
 {
     const int64_t per_view = std::min<int64_t>(ws.Kp, ws.limit);
-    const bool wide = (size_t)ws.V * (size_t)(per_view / (4 * BLOCK)) >= 1024;
+    const bool wide = (size_t)ws.V * (size_t)(per_view / (4 * BLOCK)) >= 512;
     ws.em_chunk = wide ? 4 * BLOCK : BLOCK;
     ws.em_cpv = (int)((per_view + ws.em_chunk - 1) / ws.em_chunk);
     // placement units per workgroup of k_bin_pairs: BIN_GROUP when there are many
@@ -2653,35 +2703,55 @@ void emit1_chunking(Workspace &ws)
     ws.bin_group = (size_t)ws.V * (size_t)ws.em_cpv >= 2048 ? BIN_GROUP : 1;
 }
 
-size_t bins_bytes(int V, int cpv)
+// tiles per thread of the direct binning's kernels (256 x this many cover the grid)
+static int bins_tpt(const DevGrid &g) { return g.tiles <= 256 ? 1 : g.tiles <= 512 ? 2 : 4; }
+
+// (the placement packs a rectangle's row, column and extents into bytes)
+bool bins_fit(const DevGrid &g) { return g.tiles <= BIN_MAX_TILES && g.tiles_x <= 255 && g.tiles_y <= 255; }
+
+static int bins_slices(int cpv) { return (cpv + BIN_SLICE - 1) / BIN_SLICE; }
+
+size_t bins_bytes(int V, int cpv, const DevGrid &g)
 {
-    const size_t vc = (size_t)V * cpv;
-    return (vc * 256 + vc * 4 + (size_t)V * 256 + (size_t)V + (size_t)V * (cpv + 1)) * 4;
+    const size_t vc = (size_t)V * cpv, bs = 256 * (size_t)bins_tpt(g);
+    // (views of one slice keep no sums)
+    const size_t sums = bins_slices(cpv) > 1 ? (size_t)V * bins_slices(cpv) * bs : 0;
+    return (vc * bs + vc * 4 + (size_t)V * bs + (size_t)V + (size_t)V * (cpv + 1) + sums) * 4;
 }
 
 namespace {
 struct BinPtrs {
-    uint32_t *cnt, *tot, *live, *unit;
+    uint32_t *cnt, *tot, *live, *unit, *sum;
     uint4 *info;
 };
 BinPtrs bin_ptrs(Workspace &ws)
 {
     BinPtrs b;
-    const size_t vc = (size_t)ws.V * ws.em_cpv;
+    const size_t vc = (size_t)ws.V * ws.em_cpv, bs = 256 * (size_t)bins_tpt(ws.g);
     b.cnt = ws.bins.as<uint32_t>();
-    b.info = reinterpret_cast<uint4 *>(b.cnt + vc * 256);
-    b.tot = b.cnt + vc * 256 + vc * 4;
-    b.live = b.tot + (size_t)ws.V * 256;
+    b.info = reinterpret_cast<uint4 *>(b.cnt + vc * bs);
+    b.tot = b.cnt + vc * bs + vc * 4;
+    b.live = b.tot + (size_t)ws.V * bs;
     b.unit = b.live + ws.V;
+    b.sum = b.unit + (size_t)ws.V * (ws.em_cpv + 1);
     return b;
 }
+// LDS bytes of the per-tile difference counts
+size_t bins_diff_bytes(const DevGrid &g) { return (size_t)g.tiles_y * (g.tiles_x + 1) * 4; }
 }  // namespace
 
 hipError_t launch_bin_scan(Workspace &ws, const DevGrid &g, hipStream_t st)
 {
     const BinPtrs b = bin_ptrs(ws);
-    hipLaunchKernelGGL(k_bin_scan, dim3((unsigned)ws.V), dim3(BLOCK), 0, st, ws.hist.as<uint32_t>(), 4, ws.limit,
-                       ws.em_cpv, ws.em_chunk, g.tiles, ws.bin_group, b.info, b.cnt, b.tot, b.live, b.unit);
+    const int tpt = bins_tpt(g), slices = bins_slices(ws.em_cpv);
+    const dim3 grid((unsigned)ws.V, (unsigned)slices, (unsigned)((g.tiles + BLOCK - 1) / BLOCK));
+    if (slices > 65535) return hipErrorInvalidConfiguration;
+    if (slices > 1)
+        hipLaunchKernelGGL(k_bin_scan<true>, grid, dim3(BLOCK), 0, st, ws.hist.as<uint32_t>(), 4, ws.limit, ws.em_cpv,
+                           ws.em_chunk, g.tiles, 256 * tpt, ws.bin_group, b.info, b.cnt, b.sum, b.tot, b.live,
+                           b.unit);
+    hipLaunchKernelGGL(k_bin_scan<false>, grid, dim3(BLOCK), 0, st, ws.hist.as<uint32_t>(), 4, ws.limit, ws.em_cpv,
+                       ws.em_chunk, g.tiles, 256 * tpt, ws.bin_group, b.info, b.cnt, b.sum, b.tot, b.live, b.unit);
     return hipGetLastError();
 }
 
@@ -2690,10 +2760,12 @@ hipError_t launch_bin_pairs(Workspace &ws, const DevGrid &g, hipStream_t st)
     if (ws.n_emit_chunks == 0) return hipSuccess;
     if (ws.em_chunk > BIN_CHUNK_MAX) return hipErrorInvalidValue;
     const BinPtrs b = bin_ptrs(ws);
-    hipLaunchKernelGGL(k_bin_pairs, dim3((unsigned)ws.n_emit_chunks), dim3(BLOCK), 0, st, ws.sbox.as<float4>(),
-                       ws.poff.as<uint32_t>(), ws.Kp, g, ws.em_cpv, ws.V, ws.bin_group, ws.d_chunk_off, b.info, b.cnt,
-                       b.tot,
-                       b.live, b.unit, ws.d_pbase, ws.d_pcount, ws.pval[0].as<uint32_t>());
+    const int tpt = bins_tpt(g);
+    auto kern = tpt == 1 ? k_bin_pairs<1> : tpt == 2 ? k_bin_pairs<2> : k_bin_pairs<4>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)ws.n_emit_chunks), dim3(BLOCK), bins_diff_bytes(g), st,
+                       ws.sbox.as<float4>(), ws.poff.as<uint32_t>(), ws.Kp, g, ws.em_cpv, ws.V, ws.bin_group,
+                       ws.d_chunk_off, b.info, b.cnt, b.tot, b.live, b.unit, ws.d_pbase, ws.d_pcount,
+                       ws.pval[0].as<uint32_t>());
     return hipGetLastError();
 }
 
@@ -2703,15 +2775,17 @@ hipError_t launch_emit1(const Scene &sc, Workspace &ws, const DevGrid &g, hipStr
     emit1_chunking(ws);
     const bool wide = ws.em_chunk == 4 * BLOCK;
     const int cpv = ws.em_cpv;
-    const BinPtrs b = ws.direct_bins ? bin_ptrs(ws) : BinPtrs{nullptr, nullptr, nullptr, nullptr, nullptr};
+    const BinPtrs b = ws.direct_bins ? bin_ptrs(ws)
+                                     : BinPtrs{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     auto kern = wide ? k_emit1<2, 2 * BLOCK> : k_emit1<1, BLOCK>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(ws.V * cpv)), dim3(wide ? 2 * BLOCK : BLOCK), 0, st,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(ws.V * cpv)), dim3(wide ? 2 * BLOCK : BLOCK),
+                       ws.direct_bins ? bins_diff_bytes(g) : 0, st,
                        ws.ggeo.as<GaussGeoPacked>(), sc.K, ws.Kp, ws.centres_p, g,
                        ws.sval[ws.sorted_buf].as<uint32_t>(), ew + KEPT_STRIDE, cpv, ws.srec.as<float4>(),
                        ws.sbox.as<float4>(), ws.vorder.as<uint32_t>(), ws.poff.as<uint32_t>(),
                        ws.counters.as<unsigned long long>(),
                        reinterpret_cast<unsigned long long *>(ew + KEPT_STRIDE + (size_t)ws.V * KEPT_STRIDE), ew,
-                       ws.limit, ws.vflag.as<uint32_t>(), b.cnt, b.info);
+                       ws.limit, ws.vflag.as<uint32_t>(), b.cnt, 256 * bins_tpt(g), b.info);
     return hipGetLastError();
 }
 
@@ -2729,7 +2803,8 @@ hipError_t launch_ranges(Workspace &ws, const DevGrid &g, hipStream_t st)
 {
     const size_t nr = (size_t)ws.V * g.tiles;
     ws.items_built = false;
-    if (g.tiles <= 255) {
+    // (a pair sort by one 8-bit pass leaves the list lengths as its digit totals)
+    if (ws.direct_bins || g.tiles <= 255) {
         // one 8-bit pass: ranges straight from the scanned histogram; the MLP
         // work items in the same launch
         const unsigned nbi = ws.use_items ? (unsigned)nblk((size_t)ws.n_items) : 0u;
@@ -2739,8 +2814,8 @@ hipError_t launch_ranges(Workspace &ws, const DevGrid &g, hipStream_t st)
         // the radiance prefix path's position-block marks are cleared here too
         ws.live_cleared = ws.mpos != 0xFFFFFFFFu;
         hipLaunchKernelGGL(k_ranges_items, dim3((unsigned)ws.V + nbi), dim3(BLOCK), 0, st, lens,
-                           ws.d_pbase, ws.d_pcount, g.tiles, ws.ranges.as<uint2>(), ws.torder.as<uint32_t>(),
-                           ws.d_item_off, ws.d_vinfo, ws.V, ws.n_items, ws.items.as<int4>(),
+                           ws.d_pbase, ws.d_pcount, g.tiles, ws.direct_bins ? bins_tpt(g) : 1, ws.ranges.as<uint2>(),
+                           ws.torder.as<uint32_t>(), ws.d_item_off, ws.d_vinfo, ws.V, ws.n_items, ws.items.as<int4>(),
                            ws.live_cleared ? ws.live.as<uint32_t>() : nullptr,
                            ws.live_cleared ? (live_count_offset(ws) + 3) / 4 : (size_t)0);
         ws.tiles_ordered = true;

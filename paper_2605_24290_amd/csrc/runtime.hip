@@ -988,9 +988,9 @@ static rxgs_status render_pass(rxgs_ctx *ctx, int mode, int Q, const float *tx, 
     WGROW(ctx, ws, ws.hist, sort_ws_bytes((uint32_t)VK, 32, V));
     // grids of at most BIN_MAX_TILES tiles: the first emission counts its
     // pairs per tile and the pairs are placed in their tile lists directly
-    ws.direct_bins = g.tiles <= BIN_MAX_TILES && !ctx->pair_sort;
+    ws.direct_bins = bins_fit(g) && !ctx->pair_sort;
     emit1_chunking(ws);
-    if (ws.direct_bins) WGROW(ctx, ws, ws.bins, bins_bytes(V, ws.em_cpv));
+    if (ws.direct_bins) WGROW(ctx, ws, ws.bins, bins_bytes(V, ws.em_cpv, g));
 
     if (save) {
         HIPCHK(ctx, hipMemcpyAsync(ws.centres.p, mode == RXGS_MODE_TX ? tx : rx, (size_t)V * 12,

@@ -35,8 +35,9 @@ constexpr int STAT_WORDS = 4 * STAT_SLOTS;   // four statistics, u64 each
 constexpr uint32_t SMALL_SORT = 1u << 20;  // sorts up to this length use 1024-key blocks
 constexpr int EM2_PER = 1;               // pair emission: 256-entry sub-chunks per workgroup
 constexpr int EM2_CHUNK = BLOCK * EM2_PER;
-constexpr int BIN_MAX_TILES = 255;       // grids up to this many tiles place their pairs without a pair sort
-constexpr int BIN_DIFF_WORDS = 512;      // LDS words of the per-tile difference counts (tiles_y x (tiles_x + 1))
+constexpr int BIN_MAX_TILES = 1024;      // grids up to this many tiles (at most 255 rows and columns of them) place
+                                         // their pairs without a pair sort
+constexpr int BIN_SLICE = 64;            // chunks of one view per workgroup of the direct binning's scan
 constexpr int KEPT_STRIDE = 32;          // words between the per-view kept counts the depth sort leaves
 constexpr int SORT_VALS_INDEX = 1;       // sort flag: a key's value is its index in its segment (not read)
 constexpr int SORT_VALS_ONLY = 2;        // sort flag: the sorted keys are not needed (last pass writes values only)
@@ -237,7 +238,7 @@ struct Workspace {
     // direct binning (at most BIN_MAX_TILES tiles): per chunk of the first
     // emission its pairs per tile (then its start in each tile's list), per
     // chunk (first visible entry, visible entries), per view its list
-    // lengths and its live chunks
+    // lengths and its live chunks; the scan's sums per slice of chunks
     DevBuf bins;
     bool direct_bins = false;
     int em_cpv = 0, em_chunk = 0;   // chunks of the first emission per view, kept entries per chunk
@@ -391,7 +392,8 @@ hipError_t launch_emit2(Workspace &ws, const DevGrid &g, size_t sort_words, hipS
 // direct binning: the first emission's chunking (sets em_cpv, em_chunk), the
 // bytes of the bins buffer, the per-view scan and the placement of the pairs
 void emit1_chunking(Workspace &ws);
-size_t bins_bytes(int V, int cpv);
+bool bins_fit(const DevGrid &g);
+size_t bins_bytes(int V, int cpv, const DevGrid &g);
 hipError_t launch_bin_scan(Workspace &ws, const DevGrid &g, hipStream_t st);
 hipError_t launch_bin_pairs(Workspace &ws, const DevGrid &g, hipStream_t st);
 uint32_t *emit_words(Workspace &ws);

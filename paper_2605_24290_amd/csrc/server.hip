@@ -174,6 +174,10 @@ int64_t estimate_bytes(int32_t mode, int32_t Q, int32_t N, int64_t K, int32_t H,
     b += V * P * (FAR_RECORDS * 8 + 1) + 4 * V * tiles;   // far records of the radiance prefix, counts, sub-tile marks
     b += 4 * Dpad;                            // emission-order pair keys (deterministic saved states)
     b += 4 * VK + VK / 12 + 1040 * V + 64;    // direct binning: per-chunk tile counts, extents and units
+    // ... its slices' sums and, beyond 256 tiles, wider counts: from the 12 bytes
+    // per pair of a pair sort's other copies, which it does not ask for
+    const int64_t bt = tiles <= 256 ? 1 : tiles <= 512 ? 2 : tiles <= BIN_MAX_TILES ? 4 : 0;
+    b += std::max<int64_t>(0, (std::max<int64_t>(bt, 1) - 1) * (4 * VK + 1024 * V) + bt * (VK / 16 + 1024 * V) - 12 * Dpad);
     b += 20 * (int64_t)N + 80 * V + 16 * (Dpad / SORT_TILE + 1) + 1024;   // descriptors
     b += 12 * (int64_t)Q + 16 * (int64_t)N + 8 * (int64_t)N * P;   // transmitters, receivers, power, spectra
     return b;

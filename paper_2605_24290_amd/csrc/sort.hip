@@ -157,7 +157,7 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(const uint32_t *__restrict_
     for (int r = 0; r < ITEMS; r++) {
         const bool valid = key[r] != SORT_DROP;
         const uint32_t d = (key[r] >> shift) & 255u;
-        const uint64_t m = match_key8(d, __ballot(valid));
+        const uint64_t m = match_key<8>(d, __ballot(valid));
         const uint32_t below = (uint32_t)count_below(m);
         const uint32_t before = s_wc[w][d];
         rank[r] = before + below;
