@@ -153,6 +153,25 @@ __device__ __forceinline__ float wave_sum_last(float x)
     return x;
 }
 
+// Inclusive scan over the wave: the DPP steps stay in registers, where a scan by
+// __shfl_up takes six dependent round trips through the LDS crossbar.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_shift_u32(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
+}
+
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x)
+{
+    x += dpp_shift_u32<0x111, 0xf>(x);   // row_shr:1
+    x += dpp_shift_u32<0x112, 0xf>(x);   // row_shr:2
+    x += dpp_shift_u32<0x114, 0xf>(x);   // row_shr:4
+    x += dpp_shift_u32<0x118, 0xf>(x);   // row_shr:8
+    x += dpp_shift_u32<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+    x += dpp_shift_u32<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
 // ---------------------------------------------------------------------------
 // LDS staging of one batch of a tile's list for the blend kernels.
 struct BlendStage {
@@ -247,16 +266,12 @@ __device__ __forceinline__ void stage_batch(BlendStage &st, float4 r0, const flo
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t &total, uint32_t *s_w)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t v = x;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(v, off);
-        if (lane >= off) v += y;
-    }
+    const uint32_t v = wave_scan_u32(x);
     if (lane == 63) s_w[w] = v;
     __syncthreads();
-    uint32_t pre = 0;
-    for (int i = 0; i < w; i++) pre += s_w[i];
-    total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+    const uint32_t w0 = s_w[0], w1 = s_w[1], w2 = s_w[2], w3 = s_w[3];
+    const uint32_t pre = (w > 0 ? w0 : 0u) + (w > 1 ? w1 : 0u) + (w > 2 ? w2 : 0u);
+    total = w0 + w1 + w2 + w3;
     __syncthreads();
     return pre + v - x;
 }

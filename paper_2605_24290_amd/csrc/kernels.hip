@@ -103,46 +103,58 @@ __device__ __forceinline__ void gauss_geo(const float *__restrict__ soa, int64_t
 }
 
 // the view-independent part of every Gaussian, computed once per render (in
-// FP64) and read back by the key and emission kernels, 48 bytes per Gaussian:
+// FP64) and read back by the emission kernel, 48 bytes per Gaussian in a 64-byte
+// sector of its own:
 // position and opacity, then the 3-D covariance, the squared-distance bound
 // of the support and log2 opacity rounded to FP32.  The emission gathers these
-// terms in depth order; the FP32 rounding (a relative 6e-8) moves the
+// terms in depth order (packed at 48 bytes, half the gathers touched two
+// sectors); the FP32 rounding (a relative 6e-8) moves the
 // projected conic and the binning extents by about 1e-7 relative, far below
 // their FP32 storage in the blend record, and the backward differentiates
 // the FP64 terms it recomputes from the parameters.
-struct alignas(16) GaussGeoPacked {
+struct alignas(64) GaussGeoPacked {
     float px, py, pz, o32;
     float S00, S01, S02, S11;
     float S12, S22, qmax, lo2;
+    float4 pad;   // written too: whole sectors, no read-modify-write in memory
 };
 
-// Also the cull bound of each Gaussian, qcull >= q_max trace(Sigma) (rounded
-// up): the vertical variance of any projection is at most
+// Also what the key kernel reads of each Gaussian, its position and cull bound
+// qcull >= q_max trace(Sigma) (rounded up; -1 where the opacity is below 1/255):
+// the vertical variance of any projection is at most
 // lambda_max(Sigma) / (rho^2 del^2) + 0.3 px^2 <= trace(Sigma) / (rho^2 del^2) + 0.3.
 // It also clears the render's counters and the depth sort's scratch (both
 // first used by later kernels of the stream).
 __global__ __launch_bounds__(BLOCK) void k_gauss_prep(const float *__restrict__ soa, int64_t K,
-                                                      GaussGeoPacked *__restrict__ out, float *__restrict__ qcull,
+                                                      GaussGeoPacked *__restrict__ out, float4 *__restrict__ qcull,
                                                       uint32_t *__restrict__ z0, size_t n0, uint32_t *__restrict__ z1,
                                                       size_t n1)
 {
+    __shared__ float4 s_out[4 * BLOCK];
     {
         const size_t stride = (size_t)gridDim.x * BLOCK;
         const size_t i0 = (size_t)blockIdx.x * BLOCK + threadIdx.x;
         for (size_t i = i0; i < n0; i += stride) z0[i] = 0u;
         for (size_t i = i0; i < n1; i += stride) z1[i] = 0u;
     }
-    const int64_t k = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (k >= K) return;
-    GaussGeo G;
-    gauss_geo(soa, K, k, G);
-    GaussGeoPacked o;
-    o.px = G.px; o.py = G.py; o.pz = G.pz; o.o32 = G.o32;
-    o.S00 = (float)G.S00; o.S01 = (float)G.S01; o.S02 = (float)G.S02;
-    o.S11 = (float)G.S11; o.S12 = (float)G.S12; o.S22 = (float)G.S22;
-    o.qmax = (float)G.qmax; o.lo2 = (float)G.lo2;
-    out[k] = o;
-    qcull[k] = (float)(G.qmax * (G.S00 + G.S11 + G.S22) * (1.0 + 1e-6));
+    const int t = threadIdx.x;
+    const int64_t k0 = (int64_t)blockIdx.x * BLOCK, k = k0 + t;
+    if (k < K) {
+        GaussGeo G;
+        gauss_geo(soa, K, k, G);
+        const int sw = (t >> 2) & 3;
+        s_out[4 * t + (0 ^ sw)] = make_float4(G.px, G.py, G.pz, G.o32);
+        s_out[4 * t + (1 ^ sw)] = make_float4((float)G.S00, (float)G.S01, (float)G.S02, (float)G.S11);
+        s_out[4 * t + (2 ^ sw)] = make_float4((float)G.S12, (float)G.S22, (float)G.qmax, (float)G.lo2);
+        s_out[4 * t + (3 ^ sw)] = make_float4(0.f, 0.f, 0.f, 0.f);
+        qcull[k] = make_float4(G.px, G.py, G.pz,
+                               G.o32 >= ALPHA_MIN ? (float)(G.qmax * (G.S00 + G.S11 + G.S22) * (1.0 + 1e-6)) : -1.0f);
+    }
+    __syncthreads();
+    // the workgroup's records as one run of float4
+    const int n4 = 4 * (int)max((int64_t)0, min((int64_t)BLOCK, K - k0));
+    float4 *dst = reinterpret_cast<float4 *>(out + k0);
+    for (int i = t; i < n4; i += BLOCK) dst[i] = s_out[(i & ~3) + ((i & 3) ^ ((i >> 4) & 3))];
 }
 
 __device__ __forceinline__ void gauss_geo_load(const GaussGeoPacked *__restrict__ gg, int64_t k, GaussGeo &G)
@@ -161,6 +173,7 @@ struct ViewGeo {
     uint32_t nt;   // covered tiles; 0: culled (near, faint, or off the grid)
     double u, vv, A, B, Cc;
     float4 e;      // binning box (u, v, rup, rvp) in FP32
+    int ty0, ty1, a0, a1, b1;   // covered tiles: rows, columns [a0, a1] and [0, b1] (nt > 0)
 };
 
 __device__ __forceinline__ void view_geo(const GaussGeo &G, float cx, float cy, float cz, const DevGrid &g,
@@ -203,9 +216,9 @@ __device__ __forceinline__ void view_geo(const GaussGeo &G, float cx, float cy, 
         const float rvp = (float)(sqrt(G.qmax * P.Cc) * (1.0 + PAD_REL) + PAD_ABS);
         P.e.z = rup;
         P.e.w = rvp;
-        int ty0, ty1, a0, a1, b0, b1;
-        const int nr = tile_rows(v32, rvp, g.H, ty0, ty1);
-        const int nc = nr ? tile_cols(u32, rup, g.W, g.tiles_x, a0, a1, b0, b1) : 0;
+        int b0;
+        const int nr = tile_rows(v32, rvp, g.H, P.ty0, P.ty1);
+        const int nc = nr ? tile_cols(u32, rup, g.W, g.tiles_x, P.a0, P.a1, b0, P.b1) : 0;
         P.nt = (uint32_t)(nr * nc);
     }
 }
@@ -243,17 +256,18 @@ __device__ __forceinline__ bool maybe_on_grid(float dxf, float dyf, float dzf, f
 
 // Depth keys of VPW views' tile of PER x BLOCK Gaussians (PER per thread,
 // strided so that loads and stores are coalesced; each Gaussian's terms are
-// read once for the VPW views), with the culls of k_project, and the tile's
+// read once for the VPW views), with the culls of k_project (a negative qcull.w:
+// too faint), and the tile's
 // contribution to the depth sort's digit totals: LDS counts of all four 8-bit
 // digits of the kept keys per view, added to the view's totals with one
 // atomic per nonzero count (the values, the Gaussian indices, are not
 // written: the sort's first pass takes each key's index in its view's
-// segment).  Many views: tiles of 2048 (fewer atomics), four views per
-// workgroup for large scenes (whose per-Gaussian terms do not stay in L2);
-// few views: tiles of 256 (enough workgroups).
+// segment).  From 256 tiles of 2048 on: such tiles (fewer atomics: one view of
+// 1M Gaussians took 79 us by tiles of 256, whose 4M atomics meet on 1,024
+// words, and takes 18), four views per workgroup for large scenes (whose
+// per-Gaussian terms do not stay in L2); below, tiles of 256 (enough workgroups).
 template <int PER, int VPW>
-__global__ __launch_bounds__(BLOCK) void k_keys(const GaussGeoPacked *__restrict__ gg,
-                                                const float *__restrict__ qcull, int64_t K, int64_t Kp,
+__global__ __launch_bounds__(BLOCK) void k_keys(const float4 *__restrict__ qcull, int64_t K, int64_t Kp,
                                                 const float *__restrict__ centres, DevGrid g, int V,
                                                 uint32_t *__restrict__ skey, uint32_t *__restrict__ hist)
 {
@@ -272,23 +286,18 @@ __global__ __launch_bounds__(BLOCK) void k_keys(const GaussGeoPacked *__restrict
 #pragma unroll
     for (int r = 0; r < PER; r++) {
         const int64_t k = k0 + r * BLOCK + t;
-        float4 po = make_float4(0.f, 0.f, 0.f, 0.f);
-        float qc = 0.f;
-        if (k < K) {
-            po = *reinterpret_cast<const float4 *>(gg + k);
-            qc = qcull[k];
-        }
+        float4 po = make_float4(0.f, 0.f, 0.f, -1.f);
+        if (k < K) po = qcull[k];
 #pragma unroll
         for (int vv = 0; vv < VPW; vv++) {
             const int v = v0 + vv;
             if (v >= V) break;
             uint32_t key = 0xFFFFFFFFu;
-            if (k < K) {
+            if (!(po.w < 0.f)) {
                 const float cx = centres[3 * v], cy = centres[3 * v + 1], cz = centres[3 * v + 2];
                 const float dxf = __fsub_rn(po.x, cx), dyf = __fsub_rn(po.y, cy), dzf = __fsub_rn(po.z, cz);
                 const float kf = depth_key(dxf, dyf, dzf);
-                if (!(kf < NEAR2) && po.w >= ALPHA_MIN && maybe_on_grid(dxf, dyf, dzf, kf, qc, g))
-                    key = __float_as_uint(kf);
+                if (!(kf < NEAR2) && maybe_on_grid(dxf, dyf, dzf, kf, po.w, g)) key = __float_as_uint(kf);
             }
             skey[(size_t)v * Kp + k] = key;
             if (key != 0xFFFFFFFFu)
@@ -319,7 +328,7 @@ __global__ __launch_bounds__(BLOCK) void k_keys(const GaussGeoPacked *__restrict
 // k_keys, which applies the same culls).
 template <bool SAVE, bool KEYS = true>
 __global__ __launch_bounds__(BLOCK) void k_project(
-    const GaussGeoPacked *__restrict__ gg, const float *__restrict__ qcull, int64_t K, int64_t Kp,
+    const GaussGeoPacked *__restrict__ gg, const float4 *__restrict__ qcull, int64_t K, int64_t Kp,
     const float *__restrict__ centres, int V, int vchunk, DevGrid g, uint32_t *__restrict__ skey,
     uint32_t *__restrict__ sval, float4 *__restrict__ ext, uint32_t *__restrict__ rawkey, float *__restrict__ opac,
     uint32_t *__restrict__ z0, size_t n0, uint32_t *__restrict__ z1, size_t n1)
@@ -346,7 +355,7 @@ __global__ __launch_bounds__(BLOCK) void k_project(
         } else {
             po = *reinterpret_cast<const float4 *>(gg + k);
         }
-        qc = qcull[k];
+        qc = qcull[k].w;
     }
     for (int v = v0; v < v1; v++) {
         const size_t i = (size_t)v * Kp + k;
@@ -387,9 +396,10 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, size_t n)
 // (workgroup i: chunk i / V of view i mod V, so that the workgroups resident
 // together hold the first chunks of many views, and a later chunk's
 // look-back mostly finds its predecessors done), each of NT x PER sorted
-// entries (PER consecutive ones per thread; 1024 when there
-// are many chunks, which amortises each chunk's look-back, 256 for small
-// launches, which keeps the chain of chunks short); it loads its entries'
+// entries (1024 when there are many chunks, which amortises each chunk's
+// look-back, 256 for small launches, which keeps the chain of chunks short), a
+// thread's PER entries NT apart so that a wave's stores of one entry each are
+// to adjacent addresses; it loads its entries'
 // Gaussian indices before it knows how many the sort kept (the depth sort's
 // first pass left that count per view), evaluates them (FP64, the same code as the key kernel's exports)
 // and compacts the visible ones (at least one tile covered): their depth rank
@@ -401,43 +411,18 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, size_t n)
 // slot at its rank; the view's last chunk writes the view's visible and pair
 // counts.  Errors (a look-back that does not end, more than 2^32 - 1 pairs in
 // a view) set bits of the error word, which the host checks.
+// Bound by its FP64 arithmetic and, where the scene
+// is large, by memory (a 64-byte gather, 72 bytes written per entry): 64 views
+// x 50k 88 -> 73 us, 128 views x 1M 4.04 -> 3.26 ms since the stores are
+// adjacent, the gather is one sector, the covered tiles are kept from the
+// projection and the scans run on DPP moves.  Eight waves per SIMD (one entry
+// per thread of 1024) took 87 us: two large workgroups per CU wait together.
 constexpr uint64_t EM_AGG = 1ull << 62, EM_PRE = 1ull << 63;
 constexpr int EM_SPIN_MAX = 1 << 20;
 
 __device__ __forceinline__ uint64_t em_pack(uint64_t flag, uint32_t vis, uint32_t pairs)
 {
     return flag | ((uint64_t)(vis & 0x3FFFFFFFu) << 32) | pairs;
-}
-
-// exclusive scan of two counts at once over a workgroup of NW waves
-template <int NW>
-__device__ __forceinline__ uint2 block_exclusive_scan2(uint32_t x, uint32_t y, uint2 &total, uint2 *s_w)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t a = x, b = y;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t ya = __shfl_up(a, off), yb = __shfl_up(b, off);
-        if (lane >= off) {
-            a += ya;
-            b += yb;
-        }
-    }
-    if (lane == 63) s_w[w] = make_uint2(a, b);
-    __syncthreads();
-    uint2 pre = make_uint2(0u, 0u), tot = make_uint2(0u, 0u);
-#pragma unroll
-    for (int i = 0; i < NW; i++) {
-        const uint2 c = s_w[i];
-        if (i < w) {
-            pre.x += c.x;
-            pre.y += c.y;
-        }
-        tot.x += c.x;
-        tot.y += c.y;
-    }
-    total = tot;
-    __syncthreads();
-    return make_uint2(pre.x + a - x, pre.y + b - y);
 }
 
 // NT threads per workgroup, EM1_PER entries per thread
@@ -451,7 +436,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
     uint4 *__restrict__ binfo)
 {
     constexpr int NW = NT / 64;
-    __shared__ uint2 s_w2[NW];
+    __shared__ uint2 s_w2[EM1_PER][NW];   // (visible, pairs) of each wave's entries
     __shared__ uint32_t s_vbase, s_pbase;
     extern __shared__ int s_d[];   // per-tile difference counts, tiles_y x (tiles_x + 1) (with bcnt only)
     constexpr int EM1_CHUNK = NT * EM1_PER;
@@ -461,12 +446,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
     const int v = (int)(blockIdx.x - chunk * nviews);
     const int dw = g.tiles_x + 1;   // row stride of the per-tile difference counts
     const int64_t s0 = (int64_t)chunk * EM1_CHUNK;
-    const int64_t sb = s0 + (int64_t)t * EM1_PER;
+    const int64_t sb = s0 + t;   // the thread's entries: every NT-th of the chunk
     // the chunk's sorted Gaussian indices, loaded before the kept count is
     // known (positions past it are dropped below; the index is clamped before use)
     uint32_t kk[EM1_PER], nt[EM1_PER];
 #pragma unroll
-    for (int j = 0; j < EM1_PER; j++) kk[j] = sb + j < Kp ? order[(size_t)v * Kp + sb + j] : 0xFFFFFFFFu;
+    for (int j = 0; j < EM1_PER; j++) kk[j] = sb + j * NT < Kp ? order[(size_t)v * Kp + sb + j * NT] : 0xFFFFFFFFu;
     // entries the depth sort kept for this view; only the nearest `limit` of
     // them are emitted: record whether that cut any
     const uint32_t kv = kept[(size_t)v * KEPT_STRIDE];
@@ -480,10 +465,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
     }
 #pragma unroll
     for (int j = 0; j < EM1_PER; j++)
-        if (sb + j >= (int64_t)seg_n) kk[j] = 0xFFFFFFFFu;
+        if (sb + j * NT >= (int64_t)seg_n) kk[j] = 0xFFFFFFFFu;
     const float cx = centres[3 * v], cy = centres[3 * v + 1], cz = centres[3 * v + 2];
     float4 r0[EM1_PER], r1[EM1_PER], box[EM1_PER];
-    uint32_t nvis = 0, npairs = 0;
+    uint2 rect[EM1_PER];   // ty0, ty1, a0, a1 in bytes, then b1 + 1 (read with bcnt only: at most 255 rows and columns)
+    uint2 pre[EM1_PER];    // (visible, pairs) of the wave's lower lanes
+    const int lane = t & 63, w = t >> 6;
 #pragma unroll
     for (int j = 0; j < EM1_PER; j++) {
         nt[j] = 0;
@@ -498,13 +485,31 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
                 nt[j] = P.nt;
                 box[j] = P.e;
                 blend_record(G, P, r0[j], r1[j]);
-                nvis++;
+                rect[j] = make_uint2((uint32_t)P.ty0 | (uint32_t)P.ty1 << 8 | (uint32_t)P.a0 << 16 |
+                                         (uint32_t)P.a1 << 24,
+                                     (uint32_t)(P.b1 + 1));
             }
         }
-        npairs += nt[j];
+        const uint64_t vis = __ballot(nt[j] != 0);
+        const uint32_t sum = wave_scan_u32(nt[j]);
+        pre[j] = make_uint2((uint32_t)count_below(vis), sum - nt[j]);
+        if (lane == 63) s_w2[j][w] = make_uint2((uint32_t)__popcll(vis), sum);
     }
+    __syncthreads();
+    // every wave scans the waves' counts, one per lane
     uint2 tot;
-    const uint2 pre = block_exclusive_scan2<NW>(nvis, npairs, tot, s_w2);
+    {
+        const uint2 c = lane < EM1_PER * NW ? (&s_w2[0][0])[lane] : make_uint2(0u, 0u);
+        const uint32_t cx2 = wave_scan_u32(c.x), cy2 = wave_scan_u32(c.y);
+        tot.x = (uint32_t)__builtin_amdgcn_readlane((int)cx2, 63);
+        tot.y = (uint32_t)__builtin_amdgcn_readlane((int)cy2, 63);
+        const int ws = __builtin_amdgcn_readfirstlane(w);
+#pragma unroll
+        for (int j = 0; j < EM1_PER; j++) {
+            pre[j].x += (uint32_t)__builtin_amdgcn_readlane((int)(cx2 - c.x), j * NW + ws);
+            pre[j].y += (uint32_t)__builtin_amdgcn_readlane((int)(cy2 - c.y), j * NW + ws);
+        }
+    }
     if (t < 64) {
         uint32_t evis = 0;
         uint64_t epairs = 0;
@@ -560,16 +565,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
 #pragma unroll
         for (int j = 0; j < EM1_PER; j++) {
             if (!nt[j]) continue;
-            int ty0, ty1, a0, a1, b0, b1;
-            (void)tile_rows(box[j].y, box[j].w, g.H, ty0, ty1);
-            (void)tile_cols(box[j].x, box[j].z, g.W, g.tiles_x, a0, a1, b0, b1);
-            for (int ty = ty0; ty <= ty1; ty++) {
+            const int ty1 = (rect[j].x >> 8) & 255, a0 = (rect[j].x >> 16) & 255, a1 = rect[j].x >> 24;
+            for (int ty = rect[j].x & 255; ty <= ty1; ty++) {
                 int *d = s_d + ty * dw;
                 atomicAdd(d + a0, 1);
                 atomicAdd(d + a1 + 1, -1);
-                if (b1 >= b0) {
-                    atomicAdd(d + b0, 1);
-                    atomicAdd(d + b1 + 1, -1);
+                if (rect[j].y) {
+                    atomicAdd(d, 1);
+                    atomicAdd(d + rect[j].y, -1);
                 }
             }
         }
@@ -582,18 +585,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
             for (int x = 0; x <= tx; x++) c += s_d[ty * dw + x];
             bcnt[((size_t)v * cpv + chunk) * bstride + tl] = (uint32_t)c;
         }
-    size_t q = (size_t)v * Kp + s_vbase + pre.x;
-    uint32_t po = s_pbase + pre.y;
 #pragma unroll
     for (int j = 0; j < EM1_PER; j++) {
         if (nt[j]) {
+            const size_t q = (size_t)v * Kp + s_vbase + pre[j].x;
             srec[2 * q] = r0[j];
             srec[2 * q + 1] = r1[j];
             sbox[q] = box[j];
             vorder[q] = kk[j];
-            poff[q] = po;
-            q++;
-            po += nt[j];
+            poff[q] = s_pbase + pre[j].y;
         }
     }
     if (t == 0 && s0 + EM1_CHUNK >= (int64_t)seg_n) {
@@ -982,12 +982,7 @@ __global__ __launch_bounds__(BLOCK) void k_bin_pairs(const float4 *__restrict__ 
         __syncthreads();
         if (t < BIN_WIN / 32) {   // marks before each word: one wave's scan of the 64 word counts
             const uint32_t c1 = (uint32_t)__popc(s_mark[t]);
-            uint32_t x = c1;
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t y = __shfl_up(x, off);
-                if (t >= off) x += y;
-            }
-            s_mpre[t] = x - c1;
+            s_mpre[t] = wave_scan_u32(c1) - c1;
         }
         __syncthreads();
         const uint32_t ej = s_ej;
@@ -2643,7 +2638,7 @@ hipError_t launch_project_exports(Workspace &ws, hipStream_t st)
     if (V == 0 || ws.Kp == 0) return hipSuccess;
     dim3 grid((unsigned)(ws.Kp / BLOCK), (unsigned)((V + vchunk - 1) / vchunk));
     hipLaunchKernelGGL((k_project<true, false>), grid, dim3(BLOCK), 0, st, ws.ggeo.as<GaussGeoPacked>(),
-                       ws.qcull.as<float>(), ws.K, ws.Kp, ws.centres.as<float>(), V, vchunk, ws.g, nullptr, nullptr,
+                       ws.qcull.as<float4>(), ws.K, ws.Kp, ws.centres.as<float>(), V, vchunk, ws.g, nullptr, nullptr,
                        ws.ext.as<float4>(), ws.rawkey.as<uint32_t>(), ws.opac.as<float>(), nullptr, (size_t)0,
                        nullptr, (size_t)0);
     return hipGetLastError();
@@ -2659,15 +2654,15 @@ hipError_t launch_project(const Scene &sc, const float *centres, int V, int64_t 
     // (the clears need a grid even without Gaussians)
     const unsigned nb = (unsigned)std::max<int64_t>((sc.K + BLOCK - 1) / BLOCK, 64);
     hipLaunchKernelGGL(k_gauss_prep, dim3(nb), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,
-                       ws.ggeo.as<GaussGeoPacked>(), ws.qcull.as<float>(), ws.counters.as<uint32_t>(), counter_words,
+                       ws.ggeo.as<GaussGeoPacked>(), ws.qcull.as<float4>(), ws.counters.as<uint32_t>(), counter_words,
                        ws.hist.as<uint32_t>(), sort_words);
     if (V == 0 || Kp == 0) return hipGetLastError();
-    const bool wide = (uint64_t)V * (uint64_t)(Kp / (8 * BLOCK)) >= 1024;
+    const bool wide = (uint64_t)V * (uint64_t)(Kp / (8 * BLOCK)) >= 256;
     const bool big = wide && V >= 4 && Kp >= KEYS_BIG_SCENE;
     const int per = wide ? 8 : 1, vpw = big ? 4 : 1;
     auto kern = big ? k_keys<8, 4> : wide ? k_keys<8, 1> : k_keys<1, 1>;
     hipLaunchKernelGGL(kern, dim3((unsigned)((uint64_t)((V + vpw - 1) / vpw) * (uint64_t)(Kp / (per * BLOCK)))),
-                       dim3(BLOCK), 0, st, ws.ggeo.as<GaussGeoPacked>(), ws.qcull.as<float>(), sc.K, Kp, centres, g,
+                       dim3(BLOCK), 0, st, ws.qcull.as<float4>(), sc.K, Kp, centres, g,
                        V, ws.skey[0].as<uint32_t>(), ws.hist.as<uint32_t>());
     return hipGetLastError();
 }
