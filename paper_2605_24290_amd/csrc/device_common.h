@@ -262,16 +262,22 @@ __device__ __forceinline__ void stage_batch(BlendStage &st, float4 r0, const flo
     __syncthreads();
 }
 
-// exclusive scan over the 256 threads of a workgroup; total = sum of all
+// exclusive scan over the NW waves of a workgroup; total = sum of all
+template <int NW = 4>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t &total, uint32_t *s_w)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t v = wave_scan_u32(x);
     if (lane == 63) s_w[w] = v;
     __syncthreads();
-    const uint32_t w0 = s_w[0], w1 = s_w[1], w2 = s_w[2], w3 = s_w[3];
-    const uint32_t pre = (w > 0 ? w0 : 0u) + (w > 1 ? w1 : 0u) + (w > 2 ? w2 : 0u);
-    total = w0 + w1 + w2 + w3;
+    uint32_t pre = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < NW; i++) {
+        const uint32_t c = s_w[i];
+        pre += i < w ? c : 0u;
+        tot += c;
+    }
+    total = tot;
     __syncthreads();
     return pre + v - x;
 }

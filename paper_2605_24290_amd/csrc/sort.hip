@@ -5,11 +5,11 @@
 // depth sort, and the per-view padded pair lists).  One histogram kernel reads
 // every key once and counts all digits of all passes per segment (or the
 // caller has counted them while writing the keys).  Each pass is then a
-// single kernel: the workgroup of index i takes tile i (4096 keys; segments
+// single kernel: a workgroup takes one tile (4096 keys, 1024 in short sorts; segments
 // are runs of whole tiles), ranks its keys stably, publishes its per-digit
 // counts and obtains the counts of the earlier tiles of its segment by
 // decoupled look-back, and writes its keys digit run by digit run.  Ranking is wave
-// synchronous: each wave owns a contiguous quarter of the tile, takes its keys
+// synchronous: each wave owns a contiguous part of the tile, takes its keys
 // 64 at a time in index order, matches equal digits with 8 ballots and keeps
 // running per-digit counts in LDS, so the only workgroup barriers are the ones
 // around the look-back and the LDS staging of the tile.
@@ -19,6 +19,17 @@
 // write them, so every segment's output is its surviving keys, in order, at
 // the segment's start, and the later passes only touch that prefix (the
 // segment's surviving count is the sum of its digit totals).
+//
+// Uniform segments take their tiles in turn (workgroup i: tile i / segments of
+// segment i mod segments), so that the workgroups resident together hold the
+// first tiles of many segments and a later tile's look-back finds its
+// predecessors done; in tile order the resident workgroups were a few whole
+// segments, each a chain of look-backs over all its tiles.  Tiles of 4096 have
+// 512 threads, half the rounds of 256, and stage keys and values through the
+// same LDS, so that three workgroups fit a CU.  A pass moves 16 bytes per key;
+// it is bound by the latency of its phases, not yet by memory: four passes of 64
+// segments of 50k keys 87 -> 74 us, of 128 segments of 1M 2.63 -> 2.40 ms
+// (2.4 TB/s), of one segment of 1M (tiles of 1024 before) 96 -> 71.
 //
 // Look-back progress: a workgroup only waits for tiles with a smaller index,
 // whose workgroups were dispatched earlier; they publish their aggregates
@@ -42,6 +53,7 @@ constexpr uint32_t SORT_DROP = 0xFFFFFFFFu;   // dropped key
 struct SortSeg {
     uint32_t seg_blocks;   // uniform segments of this many tiles (0: table or one segment)
     const int4 *tab;       // per 4096-key unit: (first unit of its segment, units, segment id, 0)
+    uint32_t nseg;         // uniform segments: how many, their tiles taken in turn (1: tiles in order)
     uint32_t scale;        // tiles per 4096-key unit
 };
 
@@ -94,29 +106,30 @@ __global__ __launch_bounds__(BLOCK) void k_sort_hist(const uint32_t *__restrict_
     }
 }
 
-template <int ITEMS>
-__global__ __launch_bounds__(BLOCK) void k_sort_pass(const uint32_t *__restrict__ kin,
+template <int ITEMS, int NT>
+__global__ __launch_bounds__(NT) void k_sort_pass(const uint32_t *__restrict__ kin,
                                                      const uint32_t *__restrict__ vin,
                                                      uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
                                                      uint32_t n, int pass, int passes, SortSeg sm, int flags,
                                                      const uint32_t *__restrict__ hist, uint32_t *status,
                                                      uint32_t *seg_kept, uint32_t *err, int spin_max)
 {
-    constexpr int TILEN = BLOCK * ITEMS;
+    constexpr int TILEN = NT * ITEMS, NW = NT / 64;
     constexpr int WCH = 64 * ITEMS;   // keys per wave
-    __shared__ uint32_t s_key[TILEN];
-    __shared__ uint32_t s_val[TILEN];
-    __shared__ uint32_t s_wc[4][256];   // per-wave running digit counts, then per-wave digit starts
+    __shared__ uint32_t s_kv[TILEN];    // the tile's keys, then its values, in output order
+    __shared__ uint32_t s_wc[NW][256];   // per-wave running digit counts, then per-wave digit starts
     __shared__ uint32_t s_loc[256];     // tile-local start of each digit
     __shared__ uint32_t s_glob[256];    // output start of each digit for this tile
-    __shared__ uint32_t s_w[4];
+    __shared__ uint32_t s_w[NW];
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     const int shift = 8 * pass;
-    // the workgroup's tile is its index, and its segment follows from it
-    // (segments are runs of whole tiles); workgroups are dispatched in index
-    // order, so a look-back waits only for tiles already dispatched (and the
-    // wait is bounded in any case)
-    const uint32_t tile = blockIdx.x;
+    // the workgroup's tile follows from its index, and its segment from the
+    // tile (segments are runs of whole tiles); a segment's earlier tiles have
+    // smaller workgroup indices and workgroups are dispatched in index order,
+    // so a look-back waits only for tiles already dispatched (and the wait is
+    // bounded in any case)
+    const uint32_t tile = sm.nseg > 1 ? (blockIdx.x % sm.nseg) * sm.seg_blocks + blockIdx.x / sm.nseg
+                                      : blockIdx.x;
     uint32_t seg, first;
     tile_segment(tile, sm, seg, first);
     const size_t tile0 = (size_t)tile * TILEN, seg0 = (size_t)first * TILEN;
@@ -135,10 +148,12 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(const uint32_t *__restrict_
         val[r] = !in ? 0u : (pass == 0 && (flags & SORT_VALS_INDEX)) ? (uint32_t)(idx - seg0) : vin[idx];
     }
 #pragma unroll
-    for (int ww = 0; ww < 4; ww++) s_wc[ww][t] = 0;
+    for (int q = 0; q < 256 * NW; q += NT) (&s_wc[0][0])[q + t] = 0;
+    const bool dig = t < 256;   // the digits' threads
     // digit starts in the segment (from its digit totals) and its surviving count
     uint32_t seg_n;
-    const uint32_t dbase = block_exclusive_scan(hist[((size_t)seg * passes + pass) * 256 + t], seg_n, s_w);
+    const uint32_t dbase = block_exclusive_scan<NW>(dig ? hist[((size_t)seg * passes + pass) * 256 + t] : 0u,
+                                                     seg_n, s_w);
     if (pass == 0 && seg_kept && tile == first && t == 0) seg_kept[(size_t)seg * KEPT_STRIDE] = seg_n;
     // input positions of this tile that hold keys: all (first pass), or the
     // part of the segment's surviving prefix inside the tile (later passes)
@@ -164,16 +179,20 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(const uint32_t *__restrict_
         if (valid && below == 0) s_wc[w][d] = before + (uint32_t)__popcll(m);
     }
     __syncthreads();
-    const uint32_t c0 = s_wc[0][t], c1 = s_wc[1][t], c2 = s_wc[2][t], c3 = s_wc[3][t];
-    const uint32_t cnt = c0 + c1 + c2 + c3;
+    uint32_t cw[NW], cnt = 0;
+#pragma unroll
+    for (int ww = 0; ww < NW; ww++) {
+        cw[ww] = dig ? s_wc[ww][t] : 0u;
+        cnt += cw[ww];
+    }
 
     // decoupled look-back over the earlier tiles of this segment, digit t
     uint32_t *mine = status + (size_t)tile * 256 + t;
     uint32_t excl = 0;
     bool gave_up = false;
-    if (tile == first) {
+    if (dig && tile == first) {
         __hip_atomic_store(mine, LB_PRE | cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
+    } else if (dig) {
         __hip_atomic_store(mine, LB_AGG | cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // eight predecessors in flight per step; tiles before the segment's
         // first count as an empty prefix (spin_max < 0: no look-back at all)
@@ -215,10 +234,10 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(const uint32_t *__restrict_
     // an expired wait: the digit totals of the segment's earlier tiles, counted
     // from their input keys (positions seg0 .. tile0 hold keys in every pass)
     if (__syncthreads_or(gave_up)) {
-        s_glob[t] = 0;
+        if (dig) s_glob[t] = 0;
         __syncthreads();
         const size_t e0 = (size_t)first * TILEN, e1 = (size_t)tile * TILEN;
-        for (size_t i = e0 + t; i < e1; i += BLOCK) {
+        for (size_t i = e0 + t; i < e1; i += NT) {
             const uint32_t k = kin[i];
             if (k != SORT_DROP) atomicAdd(&s_glob[(k >> shift) & 255u], 1u);
         }
@@ -233,33 +252,50 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(const uint32_t *__restrict_
 
     // digit starts in the tile
     uint32_t tile_kept;
-    const uint32_t loc = block_exclusive_scan(cnt, tile_kept, s_w);
-    s_glob[t] = first * (uint32_t)TILEN + dbase + excl;
-    s_loc[t] = loc;
-    s_wc[0][t] = loc;
-    s_wc[1][t] = loc + c0;
-    s_wc[2][t] = loc + c0 + c1;
-    s_wc[3][t] = loc + c0 + c1 + c2;
+    const uint32_t loc = block_exclusive_scan<NW>(cnt, tile_kept, s_w);
+    if (dig) {
+        s_glob[t] = first * (uint32_t)TILEN + dbase + excl;
+        s_loc[t] = loc;
+        uint32_t at = loc;
+#pragma unroll
+        for (int ww = 0; ww < NW; ww++) {
+            s_wc[ww][t] = at;
+            at += cw[ww];
+        }
+    }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ITEMS; r++) {
         if (key[r] != SORT_DROP) {
-            const uint32_t pos = s_wc[w][(key[r] >> shift) & 255u] + rank[r];
-            s_key[pos] = key[r];
-            s_val[pos] = val[r];
+            rank[r] += s_wc[w][(key[r] >> shift) & 255u];
+            s_kv[rank[r]] = key[r];
+        } else {
+            rank[r] = SORT_DROP;
         }
     }
     __syncthreads();
-    // write out digit run by digit run: consecutive slots go to consecutive addresses
-    for (uint32_t i = t; i < tile_kept; i += BLOCK) {
-        const uint32_t k = s_key[i];
-        const uint32_t d = (k >> shift) & 255u;
-        const uint32_t o = s_glob[d] + (i - s_loc[d]);
-        if (o < n) {
-            if (pass + 1 < passes || !(flags & SORT_VALS_ONLY)) kout[o] = k;
-            vout[o] = s_val[i];
+    // write out digit run by digit run: consecutive slots go to consecutive
+    // addresses; first the keys, then, through the same LDS, the values
+    uint32_t o[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
+        const uint32_t i = r * NT + t;
+        o[r] = 0xFFFFFFFFu;
+        if (i < tile_kept) {
+            const uint32_t k = s_kv[i];
+            const uint32_t d = (k >> shift) & 255u;
+            o[r] = s_glob[d] + (i - s_loc[d]);
+            if (o[r] < n && (pass + 1 < passes || !(flags & SORT_VALS_ONLY))) kout[o[r]] = k;
         }
     }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++)
+        if (rank[r] != SORT_DROP) s_kv[rank[r]] = val[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++)
+        if (o[r] < n) vout[o[r]] = s_kv[r * NT + t];
 }
 
 // Bound of a look-back wait, in polls of a predecessor's status.
@@ -273,16 +309,17 @@ int sort_spin_limit()
     return 1 << 20;
 }
 
-template <int ITEMS>
+template <int ITEMS, int NT>
 hipError_t sort_run(DevBuf *keys, DevBuf *vals, DevBuf &wsb, int &cur, uint32_t n, int bits, int nseg,
                     int64_t seg_len, const int4 *segtab, bool zeroed, bool counted, uint32_t *seg_kept,
                     int flags, hipStream_t st)
 {
-    constexpr uint32_t TILEN = BLOCK * ITEMS;
+    constexpr uint32_t TILEN = NT * ITEMS;
     const uint32_t ntiles = (n + TILEN - 1) / TILEN;
     const int passes = (bits + 7) / 8;
     SortSeg sm;
     sm.seg_blocks = seg_len > 0 ? (uint32_t)(seg_len / TILEN) : 0u;
+    sm.nseg = sm.seg_blocks && (uint64_t)sm.seg_blocks * (uint64_t)nseg == ntiles ? (uint32_t)nseg : 1u;
     sm.tab = segtab;
     sm.scale = SORT_TILE / TILEN;
     const size_t words = sort_ws_bytes(n, bits, nseg) / 4;
@@ -295,11 +332,11 @@ hipError_t sort_run(DevBuf *keys, DevBuf *vals, DevBuf &wsb, int &cur, uint32_t 
         if (e != hipSuccess) return e;
     }
     if (!counted)
-        hipLaunchKernelGGL(k_sort_hist<ITEMS>, dim3(ntiles), dim3(BLOCK), 0, st, keys[cur].as<uint32_t>(), n, passes,
+        hipLaunchKernelGGL(k_sort_hist<TILEN / BLOCK>, dim3(ntiles), dim3(BLOCK), 0, st, keys[cur].as<uint32_t>(), n, passes,
                            sm, hist);
     const int spin_max = sort_spin_limit();
     for (int p = 0; p < passes; p++) {
-        hipLaunchKernelGGL(k_sort_pass<ITEMS>, dim3(ntiles), dim3(BLOCK), 0, st, keys[cur].as<uint32_t>(),
+        hipLaunchKernelGGL((k_sort_pass<ITEMS, NT>), dim3(ntiles), dim3(NT), 0, st, keys[cur].as<uint32_t>(),
                            vals[cur].as<uint32_t>(), keys[cur ^ 1].as<uint32_t>(), vals[cur ^ 1].as<uint32_t>(), n, p,
                            passes, sm, flags, hist, status + (size_t)p * ntiles * 256, seg_kept, err, spin_max);
         cur ^= 1;
@@ -335,9 +372,9 @@ hipError_t sort_pairs_u32(DevBuf *keys, DevBuf *vals, DevBuf &wsb, int &cur, uin
     if (n == 0 || bits <= 0) return hipSuccess;
     if (bits > 32 || nseg <= 0 || (counted && !zeroed)) return hipErrorInvalidValue;
     if (sort_items_for(n) == 4)
-        return sort_run<4>(keys, vals, wsb, cur, n, bits, nseg, seg_len, segtab, zeroed, counted, seg_kept, flags,
+        return sort_run<4, BLOCK>(keys, vals, wsb, cur, n, bits, nseg, seg_len, segtab, zeroed, counted, seg_kept, flags,
                            st);
-    return sort_run<16>(keys, vals, wsb, cur, n, bits, nseg, seg_len, segtab, zeroed, counted, seg_kept, flags, st);
+    return sort_run<8, 2 * BLOCK>(keys, vals, wsb, cur, n, bits, nseg, seg_len, segtab, zeroed, counted, seg_kept, flags, st);
 }
 
 }  // namespace rxgs

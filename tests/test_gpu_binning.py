@@ -49,3 +49,39 @@ def test_binning_equals_pair_sort(H, W, K, N, monkeypatch):
     assert out[0][2].size > 100
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("K,N", [
+    (1024, 64), (1025, 65),    # 262,144 and 266,240 padded keys at 4,096 a view: the two tile sizes
+    (4097, 40),                # two tiles per segment, the second of one key
+    (20_000, 14),              # five
+    (262_145, 1), (300_001, 1),   # one segment
+])
+def test_depth_order(K, N, monkeypatch):
+    """Each view's entries in (depth key, index) order, with keys repeated; the
+    same with every look-back replaced by the direct count."""
+    import torch
+    from paper_2605_24290_amd import rxgs
+    wl = S.make_workload("c1", K=K, N=N, grid=S.Grid(45, 90, -math.pi / 2, math.pi / 45), seed=K)
+    wl.scene.means[K // 2:K // 2 + K // 4] = wl.scene.means[:K // 4]
+    got = []
+    for spin in ("", "-1"):
+        monkeypatch.setenv("RXGS_SORT_SPIN_LIMIT", spin)
+        r = renderer_for(wl)
+        saved = rxgs.Saved(r)
+        r.render(wl.rx, tx=wl.tx, mode="rx", saved=saved)
+        torch.cuda.synchronize()
+        info = saved.info()
+        V, Kp = info["V"], info["K_pad"]
+        keys = saved.export(rxgs.EXPORT_KEYS, np.uint32, (V, Kp))
+        order = saved.export(rxgs.EXPORT_ORDER, np.int32, (V, Kp))
+        nvis = saved.export(rxgs.EXPORT_NVIS, np.int32, (V,))
+        assert V == N and nvis.min() > K // 8
+        for v in range(V):
+            o = order[v, :nvis[v]].astype(np.int64)
+            both = keys[v][o].astype(np.int64) << 32 | o
+            assert (np.diff(both) > 0).all()
+        got.append([order[v, :nvis[v]] for v in range(V)])
+        saved.close()
+        r.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
