@@ -284,14 +284,6 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
 // Entries whose offsets wrap around the azimuth circle for some pixels: du
 // differs from X + u0 by delta = +-W there, and the three sums that changes
 // are added from their own wave sums (a uniform branch; such entries are few).
-// orders a wave's own LDS accesses (LDS operations of one wave complete in order)
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int BWD_LD = 68;   // floats per LDS row of 64 pixels (16-byte aligned, rows spread over the banks)
 
 template <int RC>

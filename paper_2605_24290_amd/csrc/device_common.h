@@ -262,6 +262,14 @@ __device__ __forceinline__ void stage_batch(BlendStage &st, float4 r0, const flo
     __syncthreads();
 }
 
+// orders a wave's own LDS accesses (LDS operations of one wave complete in order)
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // exclusive scan over the NW waves of a workgroup; total = sum of all
 template <int NW = 4>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t &total, uint32_t *s_w)

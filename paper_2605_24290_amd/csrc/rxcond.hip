@@ -13,11 +13,12 @@
 //                    reads the voxel the definition names), the local MLP's
 //                    layer 1 on the VALU, layer 2 on FP32 MFMA
 //                    (v_mfma_f32_32x32x2f32, one pair per lane pair), layer 3
-//                    per lane pair: (1 + alpha', beta') per channel;
-//   k_rxcond_eval    per work item: the basis by the associated-Legendre
-//                    recurrence, streamed component by component, reduced
-//                    against the modulated coefficients, then the local
-//                    modulation: the radiance of every (receiver, channel) row.
+//                    per lane pair or on MFMA: (1 + alpha', beta') per channel;
+//   k_rxcond_eval,   per work item: the basis by the associated-Legendre
+//   k_rxcond_rows    recurrence, streamed component by component or (several
+//                    channels) through LDS, reduced against the modulated
+//                    coefficients, then the local modulation: the radiance of
+//                    every (receiver, channel) row.
 // Per upload: the occupancy grid (k_rc_bounds, k_rc_splat with exact
 // integer sums, k_rc_finish) and the coefficients in walk order.
 //
@@ -38,7 +39,6 @@ namespace {
 
 constexpr int RC_H = RXGS_RXCOND_HIDDEN;
 constexpr int RC_TAB = 13;          // (l, m) table side: lmax <= 12
-constexpr int RC_CH_PASS = 8;       // channels accumulated per basis walk
 constexpr double OCC_SCALE = 68719476736.0;   // 2^36: fixed-point scale of the log-transmission sums
 
 struct RcBox {
@@ -227,7 +227,16 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_global(const float *__restrict
 // A = W2 (w2t[(32 b + t) 64 + lane] = W2[32 b + lane % 32][2 t + lane / 32])
 // and B = layer-1 outputs, so accumulator register r of block b in lane half
 // h is hidden unit 32 b + 8 (r / 4) + 4 h + r % 4 of the lane's pair; layer 3
-// as per-lane dot products over those 32 units plus one exchange.
+// as per-lane dot products over those 32 units plus one exchange, or (MM3:
+// more than 4 channels) on FP32 MFMA too, blocks of 32 outputs, with layer 2's
+// registers as B (register r of block b is step (b, r), the halves its two
+// units): accumulator registers 4 i .. 4 i + 3 are then the four outputs of
+// channel 8 ob + 2 i + h of the lane's pair.  The dot products' weights came as
+// 832 broadcast LDS reads per unit of 26 channels, as long as all the rest; one
+// channel's 32 are fewer than a block's 32 MFMAs.  The probes are evaluated
+// four at a time so that their gathers overlap.  21 receivers x 8,192 positions
+// x 26 channels 139 -> 90 us, 21 x 4,096 x 1 33 -> 29.
+template <bool MM3>
 __global__ __launch_bounds__(BLOCK) void k_rxcond_local(
     const float *__restrict__ soa, int64_t K, const float *__restrict__ rxpos, const uint32_t *__restrict__ order,
     const int4 *__restrict__ items, int nitems, const int *__restrict__ nlive, int64_t Kp,
@@ -238,14 +247,17 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_local(
 {
 #pragma clang fp contract(off)
     if (nlive) nitems = min(nitems, *nlive);
+    // one unit = (work item, one of its receivers): rpu units per item
+    const int nunits = nitems * rpu;
+    if ((int)blockIdx.x * (BLOCK / 64) >= nunits) return;   // uniform: no work, no weights to stage
     __shared__ float s_w1[RC_H * 7];
     __shared__ float s_w2[2 * 32 * 64];
     __shared__ float s_b2[RC_H];
     __shared__ double s_t[64];
     extern __shared__ float s_dyn[];
-    const int nout = 4 * C;
-    float *s_w3 = s_dyn;            // [o][h][32]: W3[o][unit of (h, slot)]
-    float *s_b3 = s_dyn + nout * RC_H;
+    const int nout = 4 * C, nob = MM3 ? (nout + 31) / 32 : 0;
+    float *s_w3 = s_dyn;            // [o][h][32]: W3[o][unit of (h, slot)]; MM3: [block][slot][lane]
+    float *s_b3 = s_dyn + (MM3 ? nob * 32 : nout) * RC_H;
     for (int i = threadIdx.x; i < RC_H * 6; i += BLOCK) s_w1[(i / 6) * 7 + i % 6] = lw1[i];
     for (int i = threadIdx.x; i < RC_H; i += BLOCK) {
         s_w1[i * 7 + 6] = lb1[i];
@@ -253,17 +265,23 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_local(
     }
     for (int i = threadIdx.x; i < 2 * 32 * 64; i += BLOCK) s_w2[i] = w2t[i];
     for (int i = threadIdx.x; i < S; i += BLOCK) s_t[i] = tprobe[i];
-    for (int i = threadIdx.x; i < nout * RC_H; i += BLOCK) {
-        const int o = i / RC_H, rem = i % RC_H, hh = rem / 32, slot = rem % 32;
-        const int b = slot / 16, r = slot % 16;
-        s_w3[i] = lw3[(size_t)o * RC_H + 32 * b + 8 * (r >> 2) + 4 * hh + (r & 3)];
+    if (MM3) {
+        for (int i = threadIdx.x; i < nob * 32 * 64; i += BLOCK) {
+            const int ln = i & 63, slot = (i >> 6) & 31, o = 32 * (i >> 11) + (ln & 31);
+            const int b = slot / 16, r = slot % 16;
+            s_w3[i] = o < nout ? lw3[(size_t)o * RC_H + 32 * b + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3)] : 0.f;
+        }
+    } else {
+        for (int i = threadIdx.x; i < nout * RC_H; i += BLOCK) {
+            const int o = i / RC_H, rem = i % RC_H, hh = rem / 32, slot = rem % 32;
+            const int b = slot / 16, r = slot % 16;
+            s_w3[i] = lw3[(size_t)o * RC_H + 32 * b + 8 * (r >> 2) + 4 * hh + (r & 3)];
+        }
     }
-    for (int i = threadIdx.x; i < nout; i += BLOCK) s_b3[i] = lb3[i];
+    for (int i = threadIdx.x; i < (MM3 ? nob * 32 : nout); i += BLOCK) s_b3[i] = i < nout ? lb3[i] : 0.f;
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5, pl = lane & 31;
     const float invS = 1.f / (float)S;
-    // one unit = (work item, one of its receivers): rpu units per item
-    const int nunits = nitems * rpu;
     for (int u = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6); u < nunits; u += gridDim.x * (BLOCK / 64)) {
         const int item = u / rpu, jj = u - item * rpu;
         const int4 it = items[item];
@@ -280,6 +298,7 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_local(
             const double rd[3] = {(double)rxx, (double)rxy, (double)rxz};
             // probes q_s = p + t_s (r - p): this half takes s = h, h + 2, ...
             float Th = 1.f, Sh = 0.f;
+#pragma unroll 4
             for (int si = h; si < S; si += 2) {
                 const double t = s_t[si];
                 bool inside = true;
@@ -331,6 +350,32 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_local(
                 h2[r] = fmaxf(acc0[r], 0.f);
                 h2[16 + r] = fmaxf(acc1[r], 0.f);
             }
+            if constexpr (MM3) {   // layer 3, 8 channels (32 outputs) at a time
+                for (int ob = 0; ob < nob; ob++) {
+                    const float4 *bb = reinterpret_cast<const float4 *>(s_b3) + 8 * ob + h;
+                    const float *wb = s_w3 + ob * 32 * 64 + lane;
+                    floatx16 y;
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        const float4 b4 = bb[2 * i];
+                        y[4 * i] = b4.x;
+                        y[4 * i + 1] = b4.y;
+                        y[4 * i + 2] = b4.z;
+                        y[4 * i + 3] = b4.w;
+                    }
+#pragma unroll
+                    for (int q = 0; q < 32; q++)
+                        y = __builtin_amdgcn_mfma_f32_32x32x2f32(wb[q * 64], h2[q], y, 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        const int c = 8 * ob + 2 * i + h;
+                        if (valid && c < C)
+                            rloc[((size_t)j * Kp + s) * C + c] =
+                                make_float4(1.f + y[4 * i], y[4 * i + 1], y[4 * i + 2], y[4 * i + 3]);
+                    }
+                }
+                continue;
+            }
             // layer 3, one channel (4 outputs) at a time
             for (int c = 0; c < C; c++) {
                 float y[4];
@@ -349,129 +394,253 @@ __global__ __launch_bounds__(BLOCK) void k_rxcond_local(
     }
 }
 
-// Basis reduction (App. E.2; Alg. 1 eval_fle) and the two modulations.  For
-// each receiver and channel pass the lane walks its half of the components:
-// X_c += ((1 + alpha) phi + beta) B_l over them, and the basis sum SB; the
-// halves are added, then s_c = (1 + alpha') X_c + beta' SB (eq.
-// combined_local summed against the basis).
+// Basis reduction (App. E.2; Alg. 1 eval_fle) and the two modulations: of a
+// position and channel c, over each half of the components,
+// X_c += ((1 + alpha) phi + beta) B_l, and the basis sum SB; the halves are
+// added, then s_c = (1 + alpha') X_c + beta' SB (eq. combined_local summed
+// against the basis).  In all of it lane half h takes half h of the
+// components, in walk order.
+
+// The basis values (Br, Bi) of a half's components at one direction (dx, dy,
+// dz), in walk order: f(step's values, two of them with m > 0).
+template <int KIND, class F>
+__device__ __forceinline__ void rc_basis_walk(float dx, float dy, float dz, int h, int lmax, const float4 *s_ct, F f)
+{
+    const float SQ2 = 1.41421356237309515f;
+    const float rh2 = dx * dx + dy * dy;
+    const float rh = sqrtf(rh2), rr = sqrtf(rh2 + dz * dz);
+    const float ir = rr > 0.f ? 1.f / rr : 0.f;
+    const float x = dz * ir, sn = rh * ir;            // cos and sin of the polar angle
+    const float cp = rh > 0.f ? dx / rh : 1.f;         // cos and sin of the azimuth
+    const float sp = rh > 0.f ? dy / rh : 0.f;
+    const float c2 = cp * cp - sp * sp, s2 = 2.f * cp * sp;
+    float pmm = h ? sn : 1.f;                  // P_m^m at m = h
+    float cm = h ? cp : 1.f, sm = h ? sp : 0.f; // cos(m ph), sin(m ph)
+    for (int m = h; m <= lmax; m += 2) {
+        float p2 = 0.f, p1 = 0.f;
+        for (int l = m; l <= lmax; l++) {
+            const float4 ct = s_ct[l * RC_TAB + m];   // (N_lm, a_lm, b_lm, -)
+            float P;
+            if (l == m) P = pmm;
+            else if (l == m + 1) P = x * (float)(2 * m + 1) * pmm;
+            else P = ct.y * x * p1 - ct.z * p2;
+            p2 = p1;
+            p1 = P;
+            const float np = ct.x * P;
+            if (m == 0) f(1, make_float2(np, 0.f), make_float2(0.f, 0.f));
+            else if (KIND == RXGS_BASIS_FLE) f(2, make_float2(np * cm, np * sm), make_float2(np * cm, -np * sm));
+            else f(2, make_float2(SQ2 * np * cm, 0.f), make_float2(SQ2 * np * sm, 0.f));
+        }
+        pmm *= (float)((2 * m + 1) * (2 * m + 3)) * sn * sn;
+        const float cn = cm * c2 - sm * s2;
+        sm = sm * c2 + cm * s2;
+        cm = cn;
+    }
+}
+
+// one component: coefficient f, modulation a = (1 + alpha, beta), basis value B
+template <int KIND>
+__device__ __forceinline__ void rc_acc(float &xr, float &xi, const float2 &f, const float4 &a, const float2 &B)
+{
+    const float tr = fmaf(a.x, f.x, fmaf(-a.y, f.y, a.z));
+    const float ti = fmaf(a.x, f.y, fmaf(a.y, f.x, a.w));
+    if (KIND == RXGS_BASIS_FLE) {
+        xr = fmaf(tr, B.x, fmaf(-ti, B.y, xr));
+        xi = fmaf(tr, B.y, fmaf(ti, B.x, xi));
+    } else {
+        xr = fmaf(tr, B.x, xr);
+        xi = fmaf(ti, B.x, xi);
+    }
+}
+
+// s_c from X_c, SB and the local modulation
+__device__ __forceinline__ float2 rc_combine(const float4 &lm, float xr, float xi, float br, float bi)
+{
+    return make_float2(lm.x * xr - lm.y * xi + lm.z * br - lm.w * bi, lm.x * xi + lm.y * xr + lm.z * bi + lm.w * br);
+}
+
+// A half wave is 32 >> lc positions of 1 << lc channels (the power of two at or
+// above C), each lane walking the basis for itself: few channels, or more
+// components or coefficients than the next kernel takes.  A unit is (work item,
+// one of its receivers, one of its 1 << lc groups of positions).  The next
+// step's operands are loaded a step ahead.
 template <int KIND>
 __global__ __launch_bounds__(BLOCK) void k_rxcond_eval(
     const float *__restrict__ soa, int64_t K, const float *__restrict__ centres, const uint32_t *__restrict__ order,
     const int4 *__restrict__ items, int nitems, const int *__restrict__ nlive, int64_t Kp,
     const float2 *__restrict__ coef, const float4 *__restrict__ rab, const float4 *__restrict__ rloc,
-    const float4 *__restrict__ ctab, int lmax, int L, int n0, int C, int rpu, float2 *__restrict__ rad,
+    const float4 *__restrict__ ctab, int lmax, int L, int n0, int C, int lc, int rpu, float2 *__restrict__ rad,
     const int4 *__restrict__ vinfo)
 {
     if (nlive) nitems = min(nitems, *nlive);
+    const int64_t nunits = ((int64_t)nitems * rpu) << lc;
+    if ((int64_t)blockIdx.x * (BLOCK / 64) >= nunits) return;   // uniform: no work
     __shared__ float4 s_ct[RC_TAB * RC_TAB];
     for (int i = threadIdx.x; i < RC_TAB * RC_TAB; i += BLOCK) s_ct[i] = ctab[i];
     __syncthreads();
-    const int lane = threadIdx.x & 63, h = lane >> 5, pl = lane & 31;
-    const float SQ2 = 1.41421356237309515f;
-    const int nunits = nitems * rpu;
-    for (int u = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6); u < nunits; u += gridDim.x * (BLOCK / 64)) {
-        const int item = u / rpu, ju = u - item * rpu;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int c = (lane & 31) & ((1 << lc) - 1), cc = min(c, C - 1);
+    const int lastC = (L - 1) * C;
+    for (int64_t u = (int64_t)blockIdx.x * (BLOCK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < nunits;
+         u += (int64_t)gridDim.x * (BLOCK / 64)) {
+        const int grp = (int)u & ((1 << lc) - 1);
+        const int uj = (int)(u >> lc);   // (items x receivers fit an int)
+        const int item = uj / rpu, ju = uj - item * rpu;
         const int4 it = items[item];
         const int view = it.x, s0 = it.y, j0 = it.z, nj = it.w & 255, nvalid = it.w >> 8;
-        if (ju >= nj) continue;
-        const bool valid = pl < nvalid;
+        const int p0 = grp * (32 >> lc);   // the unit's first position of the item's 32
+        if (ju >= nj || p0 >= nvalid) continue;
+        const int pl = p0 + ((lane & 31) >> lc);
+        const bool valid = pl < nvalid && c < C;
         const int64_t s = s0 + pl;
         int4 vr = vinfo[view];   // its (first receiver, receivers), then rows
         vr.x *= C;
         vr.y *= C;
-        const int64_t k = min((int64_t)order[(size_t)view * Kp + (valid ? s : s0)], K - 1);
+        const int64_t k = min((int64_t)order[(size_t)view * Kp + (pl < nvalid ? s : s0)], K - 1);
         const float dx = soa[k] - centres[3 * view];
         const float dy = soa[K + k] - centres[3 * view + 1];
         const float dz = soa[2 * K + k] - centres[3 * view + 2];
-        const float rh2 = dx * dx + dy * dy;
-        const float rh = sqrtf(rh2), rr = sqrtf(rh2 + dz * dz);
-        const float ir = rr > 0.f ? 1.f / rr : 0.f;
-        const float x = dz * ir, sn = rh * ir;            // cos and sin of the polar angle
-        const float cp = rh > 0.f ? dx / rh : 1.f;         // cos and sin of the azimuth
-        const float sp = rh > 0.f ? dy / rh : 0.f;
-        const float c2 = cp * cp - sp * sp, s2 = 2.f * cp * sp;
-        const float2 *crow = coef + (size_t)k * L * C;
+        const int j = j0 + ju;
+        const float2 *crow = coef + (size_t)k * L * C + cc;
+        const float4 *arow = rab + (size_t)j * L * C + cc;
+        int w = h ? n0 * C : 0;   // walk position (in rows of C)
+        float2 f0 = crow[min(w, lastC)], f1 = crow[min(w + C, lastC)];
+        float4 a0 = arow[min(w, lastC)], a1 = arow[min(w + C, lastC)];
+        float xr = 0.f, xi = 0.f, br = 0.f, bi = 0.f;
+        rc_basis_walk<KIND>(dx, dy, dz, h, lmax, s_ct, [&](int n, const float2 &B0, const float2 &B1) {
+            w += n * C;
+            const int i0 = min(w, lastC), i1 = min(w + C, lastC);
+            const float2 g0 = crow[i0], g1 = crow[i1];
+            const float4 b0 = arow[i0], b1 = arow[i1];
+            br += B0.x;
+            bi += B0.y;
+            rc_acc<KIND>(xr, xi, f0, a0, B0);
+            if (n == 2) {
+                br += B1.x;
+                bi += B1.y;
+                rc_acc<KIND>(xr, xi, f1, a1, B1);
+            }
+            f0 = g0;
+            f1 = g1;
+            a0 = b0;
+            a1 = b1;
+        });
+        br += __shfl_xor(br, 32);
+        bi += __shfl_xor(bi, 32);
+        xr += __shfl_xor(xr, 32);
+        xi += __shfl_xor(xi, 32);
+        if (valid && h == 0)
+            rad[rad_index(vr, Kp, s, (int64_t)j * C + c)] =
+                rc_combine(rloc[((size_t)j * Kp + s) * C + c], xr, xi, br, bi);
+    }
+}
+
+// Several channels (more than 4, at most RC_ROWS_L components): the wave first
+// writes the basis values of the item's 32 positions to LDS, one position per
+// lane, then takes the components one by one: a half wave is G = 32 >> lc
+// positions of 1 << lc channels, and each lane accumulates PB groups of them
+// at once.  A component's modulation is loaded once for the PB groups, their
+// coefficients are runs of C x 8 bytes, all PB loads in flight together.  A unit
+// is (work item, one of its receivers, PB of its 1 << lc groups).  Bound by the
+// coefficients' gather (8 L C bytes per position): 21 receivers x 26 channels
+// over 8,192 positions of 25 components took 760 us by the 8 channels per walk
+// of one position per lane (0.26 TB/s), 281 by the kernel above (the basis
+// walked by all 32 lanes of a position) and take 187 (4.7 TB/s).
+constexpr int RC_ROWS_L = 49;
+template <int KIND, int PB>
+__global__ __launch_bounds__(BLOCK) void k_rxcond_rows(
+    const float *__restrict__ soa, int64_t K, const float *__restrict__ centres, const uint32_t *__restrict__ order,
+    const int4 *__restrict__ items, int nitems, const int *__restrict__ nlive, int64_t Kp,
+    const float2 *__restrict__ coef, const float4 *__restrict__ rab, const float4 *__restrict__ rloc,
+    const float4 *__restrict__ ctab, int lmax, int L, int n0, int C, int lc, int rpu, float2 *__restrict__ rad,
+    const int4 *__restrict__ vinfo)
+{
+    if (nlive) nitems = min(nitems, *nlive);
+    const int npass = (1 << lc) / PB;
+    const int64_t nunits = (int64_t)nitems * rpu * npass;
+    if ((int64_t)blockIdx.x * (BLOCK / 64) >= nunits) return;   // uniform: no work
+    __shared__ float4 s_ct[RC_TAB * RC_TAB];
+    __shared__ uint32_t s_off[4][32];   // per wave and position: its coefficients' offset
+    __shared__ float2 s_sb[4][32];      // its basis sum
+    extern __shared__ float2 s_dynb[];  // [wave][component][position]: basis values
+    for (int i = threadIdx.x; i < RC_TAB * RC_TAB; i += BLOCK) s_ct[i] = ctab[i];
+    __syncthreads();
+    const int lane = threadIdx.x & 63, h = lane >> 5, wv = threadIdx.x >> 6;
+    const int c = (lane & 31) & ((1 << lc) - 1), cc = min(c, C - 1), gi = (lane & 31) >> lc, G = 32 >> lc;
+    float2 *s_b = s_dynb + (size_t)wv * L * 32;
+    const int nh = h ? L - n0 : n0, w0 = h ? n0 : 0;   // the half's components
+    for (int64_t u = (int64_t)blockIdx.x * (BLOCK / 64) + __builtin_amdgcn_readfirstlane(wv); u < nunits;
+         u += (int64_t)gridDim.x * (BLOCK / 64)) {
+        const int uj = (int)(u / npass), pass = (int)(u - (int64_t)uj * npass);
+        const int item = uj / rpu, ju = uj - item * rpu;
+        const int4 it = items[item];
+        const int view = it.x, s0 = it.y, j0 = it.z, nj = it.w & 255, nvalid = it.w >> 8;
+        const int p0 = pass * PB * G;   // the unit's first position
+        if (ju >= nj || p0 >= nvalid) continue;
+        int4 vr = vinfo[view];   // its (first receiver, receivers), then rows
+        vr.x *= C;
+        vr.y *= C;
+        const int j = j0 + ju;
+        wave_lds_fence();   // the last unit's reads
         {
-            const int j = j0 + ju;
-            const float4 *arow = rab + (size_t)j * L * C;
-            for (int c0 = 0; c0 < C; c0 += RC_CH_PASS) {
-                const int nc = min(RC_CH_PASS, C - c0);
-                float xr[RC_CH_PASS], xi[RC_CH_PASS];
-#pragma unroll
-                for (int q = 0; q < RC_CH_PASS; q++) xr[q] = xi[q] = 0.f;
-                float br = 0.f, bi = 0.f;
-                int w = h ? n0 : 0;
-                // one component: basis value (Br, Bi) at walk position w
-                auto acc_comp = [&](float Br, float Bi) {
-                    br += Br;
-                    bi += Bi;
-                    const float2 *cf = crow + (size_t)w * C + c0;
-                    const float4 *ab = arow + (size_t)w * C + c0;
-#pragma unroll
-                    for (int q = 0; q < RC_CH_PASS; q++) {
-                        if (q < nc) {
-                            const float2 f = cf[q];
-                            const float4 a = ab[q];
-                            const float tr = fmaf(a.x, f.x, fmaf(-a.y, f.y, a.z));
-                            const float ti = fmaf(a.x, f.y, fmaf(a.y, f.x, a.w));
-                            if (KIND == RXGS_BASIS_FLE) {
-                                xr[q] = fmaf(tr, Br, fmaf(-ti, Bi, xr[q]));
-                                xi[q] = fmaf(tr, Bi, fmaf(ti, Br, xi[q]));
-                            } else {
-                                xr[q] = fmaf(tr, Br, xr[q]);
-                                xi[q] = fmaf(ti, Br, xi[q]);
-                            }
-                        }
-                    }
-                    w++;
-                };
-                float pmm = h ? sn : 1.f;                  // P_m^m at m = h
-                float cm = h ? cp : 1.f, sm = h ? sp : 0.f; // cos(m ph), sin(m ph)
-                for (int m = h; m <= lmax; m += 2) {
-                    float p2 = 0.f, p1 = 0.f;
-                    for (int l = m; l <= lmax; l++) {
-                        const float4 ct = s_ct[l * RC_TAB + m];   // (N_lm, a_lm, b_lm, -)
-                        float P;
-                        if (l == m) P = pmm;
-                        else if (l == m + 1) P = x * (float)(2 * m + 1) * pmm;
-                        else P = ct.y * x * p1 - ct.z * p2;
-                        p2 = p1;
-                        p1 = P;
-                        const float np = ct.x * P;
-                        if (m == 0) {
-                            acc_comp(np, 0.f);
-                        } else if (KIND == RXGS_BASIS_FLE) {
-                            acc_comp(np * cm, np * sm);
-                            acc_comp(np * cm, -np * sm);
-                        } else {
-                            acc_comp(SQ2 * np * cm, 0.f);
-                            acc_comp(SQ2 * np * sm, 0.f);
-                        }
-                    }
-                    pmm *= (float)((2 * m + 1) * (2 * m + 3)) * sn * sn;
-                    const float cn = cm * c2 - sm * s2;
-                    sm = sm * c2 + cm * s2;
-                    cm = cn;
+            const int pl = lane & 31;
+            const int64_t k = min((int64_t)order[(size_t)view * Kp + s0 + (pl < nvalid ? pl : 0)], K - 1);
+            const float dx = soa[k] - centres[3 * view];
+            const float dy = soa[K + k] - centres[3 * view + 1];
+            const float dz = soa[2 * K + k] - centres[3 * view + 2];
+            float br = 0.f, bi = 0.f;
+            float2 *dst = s_b + w0 * 32 + pl;
+            rc_basis_walk<KIND>(dx, dy, dz, h, lmax, s_ct, [&](int n, const float2 &B0, const float2 &B1) {
+                dst[0] = B0;
+                br += B0.x;
+                bi += B0.y;
+                if (n == 2) {
+                    dst[32] = B1;
+                    br += B1.x;
+                    bi += B1.y;
                 }
-                br += __shfl_xor(br, 32);
-                bi += __shfl_xor(bi, 32);
+                dst += 32 * n;
+            });
+            br += __shfl_xor(br, 32);
+            bi += __shfl_xor(bi, 32);
+            if (h == 0) {
+                s_off[wv][pl] = (uint32_t)(k * L * C);
+                s_sb[wv][pl] = make_float2(br, bi);
+            }
+        }
+        wave_lds_fence();
+        uint32_t off[PB];   // bytes
+        float xr[PB], xi[PB];
 #pragma unroll
-                for (int q = 0; q < RC_CH_PASS; q++) {
-                    if (q < nc) {
-                        xr[q] += __shfl_xor(xr[q], 32);
-                        xi[q] += __shfl_xor(xi[q], 32);
-                    }
-                }
+        for (int p = 0; p < PB; p++) {
+            off[p] = (s_off[wv][p0 + p * G + gi] + (uint32_t)(w0 * C + cc)) * 8u;
+            xr[p] = xi[p] = 0.f;
+        }
+        const float4 *arow = rab + (size_t)j * L * C + (size_t)w0 * C + cc;
+        const float2 *brow = s_b + w0 * 32 + p0 + gi;
+        const char *cbase = reinterpret_cast<const char *>(coef);
+        for (int i = 0; i < nh; i++) {
+            const float4 a = *arow;
+            float2 f[PB];
 #pragma unroll
-                for (int q = 0; q < RC_CH_PASS; q++) {
-                    if (q < nc && valid && (q & 1) == h) {
-                        const int c = c0 + q;
-                        const float4 lm = rloc[((size_t)j * Kp + s) * C + c];
-                        const float sr = lm.x * xr[q] - lm.y * xi[q] + lm.z * br - lm.w * bi;
-                        const float si = lm.x * xi[q] + lm.y * xr[q] + lm.z * bi + lm.w * br;
-                        rad[rad_index(vr, Kp, s, (int64_t)j * C + c)] = make_float2(sr, si);
-                    }
-                }
+            for (int p = 0; p < PB; p++) {
+                f[p] = *reinterpret_cast<const float2 *>(cbase + off[p]);
+                off[p] += 8u * (uint32_t)C;
+            }
+#pragma unroll
+            for (int p = 0; p < PB; p++) rc_acc<KIND>(xr[p], xi[p], f[p], a, brow[p * G]);
+            arow += C;
+            brow += 32;
+        }
+#pragma unroll
+        for (int p = 0; p < PB; p++) {
+            const float r = xr[p] + __shfl_xor(xr[p], 32), q = xi[p] + __shfl_xor(xi[p], 32);
+            const int pl = p0 + p * G + gi;
+            if ((p & 1) == h && c < C && pl < nvalid) {
+                const int64_t s = s0 + pl;
+                const float2 sb = s_sb[wv][pl];
+                rad[rad_index(vr, Kp, s, (int64_t)j * C + c)] =
+                    rc_combine(rloc[((size_t)j * Kp + s) * C + c], r, q, sb.x, sb.y);
             }
         }
     }
@@ -595,21 +764,30 @@ hipError_t launch_rxcond_pairs(const Scene &sc, const RxCond &m, Workspace &ws, 
     const unsigned blocks = (unsigned)std::min<int64_t>(((int64_t)nmax * rpu + 3) / 4, 256 * 8);
     const float *P = m.params.as<float>();
     RcBox box = rc_box(m);
-    const size_t lds = (size_t)(4 * m.C * RC_H + 4 * m.C) * 4;
-    hipLaunchKernelGGL(k_rxcond_local, dim3(blocks), dim3(BLOCK), lds, st, sc.soa.as<float>(), sc.K, ws.rxpos_p,
+    const bool mm3 = m.C > 4;
+    const size_t nout3 = mm3 ? (4 * (size_t)m.C + 31) / 32 * 32 : 4 * (size_t)m.C;
+    const size_t lds = (nout3 * RC_H + nout3) * 4;
+    auto local = mm3 ? k_rxcond_local<true> : k_rxcond_local<false>;
+    hipLaunchKernelGGL(local, dim3(blocks), dim3(BLOCK), lds, st, sc.soa.as<float>(), sc.K, ws.rxpos_p,
                        ws.vorder.as<uint32_t>(), items, nmax, nlive, ws.Kp, m.occ.as<float>(), m.G, box,
                        m.tprobe.as<double>(), m.S, P + m.off.l1, P + m.off.lb1, m.w2t.as<float>(), P + m.off.lb2,
                        P + m.off.l3, P + m.off.lb3, m.C, rpu, ws.rloc.as<float4>());
-    if (m.kind == RXGS_BASIS_FLE)
-        hipLaunchKernelGGL(k_rxcond_eval<RXGS_BASIS_FLE>, dim3(blocks), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,
-                           ws.centres_p, ws.vorder.as<uint32_t>(), items, nmax, nlive, ws.Kp, m.coef.as<float2>(),
-                           ws.rab.as<float4>(), ws.rloc.as<float4>(), m.ctab.as<float4>(), m.lmax, m.L, m.n0, m.C,
-                           rpu, ws.rad.as<float2>(), ws.d_vinfo);
-    else
-        hipLaunchKernelGGL(k_rxcond_eval<RXGS_BASIS_SH>, dim3(blocks), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,
-                           ws.centres_p, ws.vorder.as<uint32_t>(), items, nmax, nlive, ws.Kp, m.coef.as<float2>(),
-                           ws.rab.as<float4>(), ws.rloc.as<float4>(), m.ctab.as<float4>(), m.lmax, m.L, m.n0, m.C,
-                           rpu, ws.rad.as<float2>(), ws.d_vinfo);
+    // lanes per position: the power of two at or above C
+    int lc = 0;
+    while ((1 << lc) < m.C) lc++;
+    const bool fle = m.kind == RXGS_BASIS_FLE;
+    // (offsets are 32-bit bytes; the basis values fit the LDS of three workgroups per CU)
+    const bool rows = m.C > 4 && m.L <= RC_ROWS_L && (uint64_t)sc.K * m.L * m.C * 8 < (1ull << 32);
+    const int pb = lc == 3 ? 8 : 16;
+    auto kern = rows ? (pb == 8 ? (fle ? k_rxcond_rows<RXGS_BASIS_FLE, 8> : k_rxcond_rows<RXGS_BASIS_SH, 8>)
+                                : (fle ? k_rxcond_rows<RXGS_BASIS_FLE, 16> : k_rxcond_rows<RXGS_BASIS_SH, 16>))
+                     : (fle ? k_rxcond_eval<RXGS_BASIS_FLE> : k_rxcond_eval<RXGS_BASIS_SH>);
+    const int64_t units = (int64_t)nmax * rpu * (rows ? (1 << lc) / pb : 1 << lc);
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min<int64_t>((units + 3) / 4, 256 * 8)), dim3(BLOCK),
+                       rows ? (size_t)4 * m.L * 32 * 8 : 0, st, sc.soa.as<float>(), sc.K, ws.centres_p,
+                       ws.vorder.as<uint32_t>(), items, nmax, nlive, ws.Kp, m.coef.as<float2>(), ws.rab.as<float4>(),
+                       ws.rloc.as<float4>(), m.ctab.as<float4>(), m.lmax, m.L, m.n0, m.C, lc, rpu,
+                       ws.rad.as<float2>(), ws.d_vinfo);
     return hipGetLastError();
 }
 
