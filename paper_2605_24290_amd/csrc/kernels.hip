@@ -2526,6 +2526,268 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 
     }
 }
 
+// Few workgroups (at most BLEND_FEW_MAX, two per CU; renders that keep no
+// state): the kernel above then ends with its longest tiles, whose waves walk
+// their lists alone on their SIMDs, an entry in about 330 cycles.  Here a tile
+// has eight waves of 8 x 4 pixels, and a wave's halves take every second entry
+// of its list, each lane one pixel: a step evaluates eight entries with four
+// exponentials per lane, and the halves' weights meet by one lane swap per
+// pair of entries, for the transmittance both halves carry (the serial chain of
+// a step, five instructions per entry).  Half a sub-tile's list is shorter too,
+// and the matrix instruction takes the halves' weights as its operand, one per
+// pair of entries.  Weights, transmittances and sums are those of the kernel
+// above, bit for bit.  21 views x 26 channels on 10 tiles (420 workgroups, lists
+// of up to 6,000 entries walked whole) 834 -> 117 us, 21 receivers of one view
+// on 138 tiles (276) 37 -> 28; but 64 receivers (552, a second round of
+// workgroups) 35 -> 40.  Batches of 256 entries took 175, 31 and 42 us, three
+// workgroups per CU (80 registers, 29 spilled) 172, 35 and 48.
+constexpr int FEW_THREADS = 512;
+struct FewStage {
+    float4 r0[FEW_THREADS + 1];  // as BlendStage; the last one: an entry of weight 0, which fills a list's last group
+    float4 r1[FEW_THREADS + 1];
+    uint32_t p[FEW_THREADS];
+    uint2 roff[FEW_THREADS + 1]; // offset of the entry's radiance (top bit: none)
+    unsigned short list[8][FEW_THREADS + 8];
+    int wcnt[8][8], ncnt[8][8];  // per source wave and sub-tile: entries, those below the position prefix
+};
+
+// the eight-wave tiling's mask (see subtile_mask): bit w set when the entry can
+// reach wave w's 8 x 4 sub-tile (rows 4 (w % 2) .. of 8 x 8 block w / 2)
+__device__ __forceinline__ int subtile_mask8(const float4 &r0, const float4 &r1, int wide, int tx, int ty)
+{
+    if (wide) return 0xFF;
+    float lo = r1.w - (-7.99435343685886f);   // log2 o - log2(1/255)
+    if (!(lo >= -1e-3f)) return 0;
+    lo = fmaxf(lo, 0.f) + 1e-3f;
+    const float muu = -r1.x, muv = -0.5f * r1.y, mvv = -r1.z;
+    const float det = muu * mvv - muv * muv;
+    if (!(det > 0.f)) return 0xFF;
+    const float ru = sqrtf(lo * mvv / det) * 1.001f + 0.05f;
+    const float rv = sqrtf(lo * muu / det) * 1.001f + 0.05f;
+    const float u = r0.x + r0.y, v = r0.z + r0.w;
+    const float c0 = (float)(tx * TILE), r0f = (float)(ty * TILE);
+    int m = 0;
+#pragma unroll
+    for (int w = 0; w < 8; w++) {
+        const float cl = c0 + 8.f * (float)((w >> 1) & 1), rl = r0f + 8.f * (float)(w >> 2) + 4.f * (float)(w & 1);
+        const bool hit = (u + ru >= cl) && (u - ru <= cl + 7.f) && (v + rv >= rl) && (v - rv <= rl + 3.f);
+        m |= hit ? (1 << w) : 0;
+    }
+    return m;
+}
+
+__global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_blend_fwd_few(
+    const float4 *__restrict__ srec, const uint32_t *__restrict__ pval, const uint2 *__restrict__ ranges,
+    const float2 *__restrict__ rad, const int4 *__restrict__ chunks, int64_t Kp, DevGrid g, float *__restrict__ C,
+    float *__restrict__ part, const uint32_t *__restrict__ torder, const uint8_t *__restrict__ live,
+    uint32_t *__restrict__ vflag, uint32_t mpos, FarState fs, const int4 *__restrict__ vinfo, int nch)
+{
+    __shared__ FewStage st;
+    __shared__ float s_red[4][16][3];
+    // grid: (chunk, rank of the tile in its view's longest-first order)
+    const int4 ch = chunks[blockIdx.x];
+    const int tile = torder ? (int)torder[(size_t)ch.x * g.tiles + blockIdx.y] : (int)blockIdx.y;
+    const int view = ch.x, j0 = ch.y, nrx = ch.z;
+    const int ty = tile / g.tiles_x, tx = tile - ty * g.tiles_x;
+    const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, h = lane >> 5;
+    const int row = ty * TILE + 8 * (wv >> 2) + 4 * (wv & 1) + ((lane & 31) >> 3);
+    const int col = tx * TILE + 8 * ((wv >> 1) & 1) + (lane & 7);
+    const bool inside = row < g.H && col < g.W;
+    const float rowf = (float)row, colf = (float)col;
+    const float Wf = (float)g.W, halfW = 0.5f * (float)g.W;
+    const uint2 rg = ranges[(size_t)view * g.tiles + tile];
+    const int64_t view_end = ((int64_t)view + 1) * Kp;
+    // the transmittance while the pixel is open; 0 outside the grid and once it
+    // fell below T_EPS, so that later weights T w vanish by themselves
+    float T = inside ? 1.f : 0.f;
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; r++) acc[r] = 0.f;
+    if (t == 0) {
+        st.r0[FEW_THREADS] = make_float4(0.f, 0.f, 0.f, 0.f);
+        st.r1[FEW_THREADS] = make_float4(0.f, 0.f, 0.f, -1e30f);
+        st.roff[FEW_THREADS] = make_uint2(0u, 0x80000000u);
+    }
+    const size_t P = (size_t)g.H * g.W;
+    const size_t pix = (size_t)row * g.W + col;
+    int fcount = 0;
+    uint2 *myrec = (inside && h == 0 && mpos != 0xFFFFFFFFu) ? fs.rec + ((size_t)view * P + pix) * FAR_REC : nullptr;
+    int4 vr = vinfo[view];
+    vr.x *= nch;
+    vr.y *= nch;
+    // the lane's radiance element of an entry's run of rows
+    const float *rad_l = reinterpret_cast<const float *>(rad + (size_t)vr.x * Kp + (j0 - vr.x)) +
+                         min(lane & 31, 2 * nrx - 1);
+    auto rad_of = [&](int e) {
+        const uint2 o = st.roff[e];
+        const float x = rad_l[((size_t)(o.y & 0x7FFFFFFFu) << 32) | o.x];
+        return (int)o.y < 0 ? 0.f : x;
+    };
+
+    for (uint32_t base = rg.x; base < rg.y; base += FEW_THREADS) {
+        // stage a batch, and build the waves' lists of the entries that can reach them
+        const bool has = (uint32_t)t < rg.y - base;
+        int m = 0;
+        bool nearp = true, wide = false;
+        if (has) {
+            const uint32_t p = min(pval[base + t], (uint32_t)(view_end - 1));
+            float4 q0 = srec[2 * (size_t)p];
+            const float4 q1 = srec[2 * (size_t)p + 1];
+            const int64_t s = max((int64_t)p - (int64_t)view * Kp, (int64_t)0);
+            nearp = s < (int64_t)mpos;
+            const bool used = (live == nullptr || live[p / MLP_PAIRS] != 0) && nearp;
+            const uint64_t o = (uint64_t)s * (uint64_t)(2 * vr.y);
+            st.roff[t] = used ? make_uint2((uint32_t)o, (uint32_t)(o >> 32)) : make_uint2(0u, 0x80000000u);
+            // representative of the azimuth closest to this tile's centre
+            const float tcol = (float)(tx * TILE) + 7.5f;
+            q0.x = fmaf(rintf((tcol - q0.x) / Wf), Wf, q0.x);
+            wide = fabsf(tcol - (q0.x + q0.y)) >= halfW - 9.0f;
+            st.r0[t] = q0;
+            st.r1[t] = q1;
+            st.p[t] = p;
+            m = subtile_mask8(q0, q1, wide, tx, ty);
+        }
+        uint64_t bal[8];
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+            bal[b] = __ballot((m >> b) & 1);
+            const uint64_t nb = __ballot(((m >> b) & 1) && nearp);
+            if (lane == 0) {
+                st.wcnt[wv][b] = (int)__popcll(bal[b]);
+                st.ncnt[wv][b] = (int)__popcll(nb);
+            }
+        }
+        const bool any_wide = __syncthreads_or(wide);
+        // lane 8 w + b holds source wave w's counts of sub-tile b; summed over w
+        // (ten bits each): the entries of earlier waves, all, those below the prefix
+        int cs = (&st.wcnt[0][0])[lane];
+        cs = ((lane >> 3) < wv ? cs : 0) | cs << 10 | (&st.ncnt[0][0])[lane] << 20;
+#pragma unroll
+        for (int d = 8; d < 64; d *= 2) cs += __shfl_xor(cs, d);
+#pragma unroll
+        for (int b = 0; b < 8; b++)
+            if ((m >> b) & 1)
+                st.list[b][(__builtin_amdgcn_readlane(cs, b) & 1023) + count_below(bal[b])] = (unsigned short)t;
+        const int own = __builtin_amdgcn_readlane(cs, wv);
+        const int n = (own >> 10) & 1023, i_far = own >> 20;
+        __syncthreads();
+        if (n > 0 && __any(T > 0.f)) {
+            if (lane < 8) st.list[wv][n + lane] = FEW_THREADS;
+            wave_lds_fence();
+            const unsigned short *lp = &st.list[wv][h];
+            int e[4];
+            float ra[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) e[k] = lp[2 * k];
+#pragma unroll
+            for (int k = 0; k < 4; k++) ra[k] = rad_of(e[k]);
+            int i0 = 0;
+            do {
+                float4 r0[4], r1[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    r0[k] = st.r0[e[k]];
+                    r1[k] = st.r1[e[k]];
+                }
+                // the next group's entries and radiance, a group ahead
+                const unsigned short *ln = lp + (i0 + 8 < n ? i0 + 8 : i0);
+                int en[4];
+                float rn[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) en[k] = ln[2 * k];
+#pragma unroll
+                for (int k = 0; k < 4; k++) rn[k] = rad_of(en[k]);
+                __builtin_amdgcn_sched_barrier(0);
+                float du[4], w[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) du[k] = (colf - r0[k].x) - r0[k].y;
+                if (any_wide) {   // uniform
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        du[k] = du[k] >= halfW ? du[k] - Wf : du[k];
+                        du[k] = du[k] < -halfW ? du[k] + Wf : du[k];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const float dv = (rowf - r0[k].z) - r0[k].w;
+                    const float wr = fminf(W_MAX, __builtin_amdgcn_exp2f(blend_exponent(du[k], dv, r1[k])));
+                    w[k] = wr >= ALPHA_MIN ? wr : 0.f;
+                }
+                float b[4];   // the lane's B elements: T w of its half's entries
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    // both halves' weights, in list order
+                    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(w[k]), __float_as_uint(w[k]), false,
+                                                                     false);
+                    const float w0 = __uint_as_float(sw[0]), w1 = __uint_as_float(sw[1]);
+                    const float t0 = T * w0;
+                    T = T * (1.f - w0);
+                    T = T < T_EPS ? 0.f : T;
+                    const float t1 = T * w1;
+                    T = T * (1.f - w1);
+                    T = T < T_EPS ? 0.f : T;
+                    b[k] = h ? t1 : t0;
+                    if (i0 + 2 * k + 1 >= i_far) {   // uniform: entries past the position prefix are recorded
+                        const float tt[2] = {t0, t1};
+#pragma unroll
+                        for (int q = 0; q < 2; q++)
+                            if (i0 + 2 * k + q >= i_far && tt[q] > 0.f) {
+                                if (fcount < FAR_REC && myrec) {
+                                    const uint32_t pe = st.p[st.list[wv][i0 + 2 * k + q]];
+                                    myrec[fcount] = make_uint2(__float_as_uint(tt[q]), pe);
+                                    fs.mark[pe / MLP_PAIRS] = 1;
+                                }
+                                ++fcount;
+                            }
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[k], b[k], acc, 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    e[k] = en[k];
+                    ra[k] = rn[k];
+                }
+                i0 += 8;
+            } while (i0 < n && __any(T > 0.f));
+        }
+        if (!__syncthreads_or(T > 0.f)) break;
+    }
+    // (as the kernel above; its votes also order the walks before the LDS below)
+    if (__syncthreads_or(T > 0.f) && t == 0 && (vflag[view] & 1u)) atomicOr(vflag + view, 2u);
+    if (mpos != 0xFFFFFFFFu) {
+        if (inside && h == 0) fs.cnt[(size_t)view * P + pix] = (uint8_t)min(fcount, 255);
+        const int any_rec = __syncthreads_or(fcount > 0 && fcount <= FAR_REC);
+        const int any_ovf = __syncthreads_or(fcount > FAR_REC);
+        if (t == 0) {
+            fs.tile[(size_t)view * g.tiles + tile] = any_rec ? 1 : 0;
+            if (any_ovf || any_rec) atomicOr(vflag + view, any_ovf ? 12u : 8u);
+        }
+    }
+    // the 8 x 8 block's two waves together, as the kernel above stores and sums
+    // it: the lower rows' sums through LDS (the staging is over)
+    float *s_x = reinterpret_cast<float *>(st.r0) + (size_t)(wv >> 1) * 16 * 64 + lane;   // r0 and r1: 16 KB
+    if (wv & 1)
+#pragma unroll
+        for (int r = 0; r < 16; r++) s_x[r * 64] = acc[r];
+    __syncthreads();
+    if (!(wv & 1)) {
+        floatx16 a1;
+#pragma unroll
+        for (int r = 0; r < 16; r++) a1[r] = s_x[r * 64];
+        blend_store_rows<0>(acc, a1, C, P, g, j0, nrx, row, col, s_red[wv >> 1]);
+    }
+    __syncthreads();
+    if (t < 16 * 3) {
+        const int r = t / 3, c = t % 3;
+        if (r < nrx) {
+            const float v = ((s_red[0][r][c] + s_red[1][r][c]) + s_red[2][r][c]) + s_red[3][r][c];
+            part[((size_t)(j0 + r) * g.tiles + tile) * 3 + c] = v;
+        }
+    }
+}
+
 // one wave per receiver; lanes take tiles in a fixed stride, then a fixed
 // butterfly, so the result does not depend on scheduling
 // part: per (row, tile) nsub partials of (power, Re, Im), the sub-tiles of a
@@ -3017,6 +3279,12 @@ static void blend_launch(Workspace &ws, float *C, bool save, hipStream_t st, boo
                                ws.rad.as<float2>(), ws.d_chunks, ws.Kp, ws.g, C, nullptr, nullptr,
                                ws.part.as<float>(), nullptr, tord, ws.lazy ? ws.live.as<uint8_t>() : nullptr,
                                ws.vflag.as<uint32_t>(), mpos, fs, ws.d_vinfo, ws.Ch);
+        else if (NB == 1 && (int64_t)grid.x * grid.y <= BLEND_FEW_MAX)
+            hipLaunchKernelGGL(k_blend_fwd_few, grid, dim3(FEW_THREADS), 0, st, ws.srec.as<float4>(),
+                               ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.rad.as<float2>(),
+                               ws.d_chunks, ws.Kp, ws.g, C, ws.part.as<float>(), tord,
+                               ws.lazy ? ws.live.as<uint8_t>() : nullptr, ws.vflag.as<uint32_t>(), mpos, fs, ws.d_vinfo,
+                               ws.Ch);
         else
             hipLaunchKernelGGL((k_blend_fwd_multi<NB, false>), grid, dim3(BLOCK), 0, st, ws.srec.as<float4>(),
                                ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.rad.as<float2>(),

@@ -24,6 +24,7 @@ constexpr int MLP_IN = ENC + FEAT;
 constexpr int MLP_RG = 16;               // receivers per MLP work item
 constexpr int MLP_PAIRS = 32;            // sorted positions per MLP work item
 constexpr int64_t BLEND_WIDE_MIN = 16384;   // workgroups of 16 rows from which a blend chunk holds 32 rows
+constexpr int64_t BLEND_FEW_MAX = 512;   // workgroups up to which a tile's blend has eight waves (two per CU)
 constexpr int LAZY_MIN_RX = 4;           // receivers of a TX view for its weights-only pass
 constexpr int64_t NEAR_LIMIT = 4096;     // nearest depth-sorted entries emitted per view first
 constexpr uint32_t PREFIX_POS = 4096;    // sorted positions whose radiance the first blend pass gets (TX)

@@ -81,3 +81,31 @@ def test_wide_chunks_bits():
         Cp, Pp, _ = r.render(wl.rx[a:b], tx=wl.tx, mode="tx")
         assert torch.equal(Cp, C[a:b]) and torch.equal(Pp, P[a:b]), a
     r.close()
+
+
+@pytest.mark.parametrize("H,W,K,N,faint", [
+    (18, 72, 9000, 21, True),     # lists of several staged batches, never saturated, past the prefix
+    (18, 72, 9000, 21, False),
+    (45, 90, 3000, 16, True),     # full sphere: entries around the azimuth circle; ragged tiles
+    (5, 6, 700, 2, True),         # one tile, most of it outside the grid
+    (90, 360, 513, 33, False),    # one entry past a batch at most
+])
+def test_few_workgroups_bits(H, W, K, N, faint):
+    """Launches of few workgroups (eight waves per tile) against saving renders of
+    the same receivers, which take four: spectra and powers bit for bit."""
+    import torch
+    from paper_2605_24290_amd import rxgs
+    el0 = 0.0 if H * 4 == W else -math.pi / 2
+    wl = S.make_workload("c1", K=K, N=N, grid=S.Grid(H, W, el0, (math.pi / 2 if el0 == 0.0 else math.pi) / H), seed=K + N)
+    if faint:
+        wl.scene.logits[:] -= 4.0
+    r = renderer_for(wl)
+    C, P, _ = r.render(wl.rx, tx=wl.tx, mode="tx")
+    C, P = C.clone(), P.clone()
+    st = rxgs.Saved(r)
+    Cs, Ps, _ = r.render(wl.rx, tx=wl.tx, mode="tx", saved=st)
+    torch.cuda.synchronize()
+    assert float(C.abs().max()) > 0
+    assert torch.equal(C, Cs) and torch.equal(P, Ps)
+    st.close()
+    r.close()
