@@ -1740,10 +1740,20 @@ hipError_t launch_rad_bwd(const Scene &sc, Workspace &ws, float *grad, hipStream
     return hipGetLastError();
 }
 
+// virtual items per work item: enough that each holds at most MLPB_RSUB receivers
+// (the deterministic backward keeps whole items: one slot per receiver group)
+static int mlp_bwd_nsub(const Workspace &ws)
+{
+    return ws.det ? 1 : std::max(1, (std::min(ws.R_max, MLP_RG) + MLPB_RSUB - 1) / MLPB_RSUB);
+}
+
+// a wave per virtual item, up to one per SIMD.  (Counted by whole items, 32
+// receivers of one view over a prefix of 4,096 positions had 256 waves on 64
+// CUs, 150 us; with 1,024 75, with two or one receivers per virtual item 87.)
 int mlp_bwd_waves(const Workspace &ws)
 {
-    const int want = (ws.n_items + 3) / 4;
-    return 4 * std::max(1, std::min(want, 256));   // one wave per SIMD fits (372 registers a lane)
+    const int64_t want = ((int64_t)ws.n_items * mlp_bwd_nsub(ws) + 3) / 4;
+    return 4 * (int)std::max<int64_t>(1, std::min<int64_t>(want, 256));   // one wave per SIMD fits (372 registers a lane)
 }
 
 hipError_t launch_mlp_bwd(const Scene &sc, const Mlp &m, Workspace &ws, float *gfeat, float *gmlp, hipStream_t st)
@@ -1754,18 +1764,16 @@ hipError_t launch_mlp_bwd(const Scene &sc, const Mlp &m, Workspace &ws, float *g
     const int nwaves = mlp_bwd_waves(ws);
     const bool far = ws.mpos != 0xFFFFFFFFu;   // the forward evaluated a radiance prefix first
     if (far && (int64_t)ws.n_items + ws.n_items_far >= (1ll << 31)) return hipErrorInvalidValue;
-    // virtual items per work item: enough that each holds at most MLPB_RSUB receivers
-    // (the deterministic backward keeps whole items: one slot per receiver group)
-    const int nsub = ws.det ? 1 : (std::min(ws.R_max, MLP_RG) + MLPB_RSUB - 1) / MLPB_RSUB;
+    const int nsub = mlp_bwd_nsub(ws);
     const int64_t nall = (int64_t)ws.n_items + (far ? ws.n_items_far : 0);
-    if (nall > INT32_MAX / std::max(nsub, 1)) return hipErrorInvalidValue;   // virtual item indices are int
+    if (nall > INT32_MAX / nsub) return hipErrorInvalidValue;   // virtual item indices are int
     // the list of live virtual items (in the reduction scratch, first written
     // after the MLP backward) when every item holds one receiver (views of
     // one receiver: their live items are few and sit at the start of each
     // view's items) and there are at most 256 chunks of 1024; items of several
     // receivers are split into virtual items, which the scattered order
     // already spreads well (the list's two launches would cost more)
-    const int64_t nvirt_max = nall * std::max(nsub, 1);
+    const int64_t nvirt_max = nall * nsub;
     const int64_t nchunk = (nvirt_max + 4 * BLOCK - 1) / (4 * BLOCK);
     constexpr size_t LIST_AT = 512;   // u32 words: chunk counts, the list length, then the list
     const bool ranked = ws.R_max == 1 && nchunk > 0 && nchunk <= BLOCK &&
@@ -1775,10 +1783,10 @@ hipError_t launch_mlp_bwd(const Scene &sc, const Mlp &m, Workspace &ws, float *g
     const int *count2 = far ? far_count(ws) : nullptr;
     if (ranked) {
         hipLaunchKernelGGL(k_live_list<false>, dim3((unsigned)nchunk), dim3(BLOCK), 0, st, ws.items.as<int4>(),
-                           ws.n_items, items2, count2, std::max(nsub, 1), ws.Kp, ws.live.as<uint8_t>(), lw,
+                           ws.n_items, items2, count2, nsub, ws.Kp, ws.live.as<uint8_t>(), lw,
                            lw + BLOCK, lw + LIST_AT);
         hipLaunchKernelGGL(k_live_list<true>, dim3((unsigned)nchunk), dim3(BLOCK), 0, st, ws.items.as<int4>(),
-                           ws.n_items, items2, count2, std::max(nsub, 1), ws.Kp, ws.live.as<uint8_t>(), lw,
+                           ws.n_items, items2, count2, nsub, ws.Kp, ws.live.as<uint8_t>(), lw,
                            lw + BLOCK, lw + LIST_AT);
     }
     if (nall > 0 && ws.det) {
@@ -1787,7 +1795,7 @@ hipError_t launch_mlp_bwd(const Scene &sc, const Mlp &m, Workspace &ws, float *g
         hipLaunchKernelGGL(k_mlp_bwd<true>, dim3((unsigned)(nwaves / 4)), dim3(BLOCK), 0, st, ws.Lp.as<float>(),
                            ws.Gp.as<float>(), m.w2a.as<float>(), m.w2b.as<float>(), m.tab.as<float4>(), W3,
                            ws.vorder.as<uint32_t>(), ws.items.as<int4>(), ws.n_items, items2, count2,
-                           std::max(nsub, 1), ws.Kp, sc.K, ws.live.as<uint8_t>(), ranked ? lw + LIST_AT : nullptr,
+                           nsub, ws.Kp, sc.K, ws.live.as<uint8_t>(), ranked ? lw + LIST_AT : nullptr,
                            ranked ? lw + BLOCK : nullptr, ws.dS.as<float2>(), ws.dL.as<float>(),
                            ws.dG.as<float>(), ws.mpart.as<float>(), det);
         const hipError_t e = launch_det_mlp_gather(ws, st);
@@ -1796,7 +1804,7 @@ hipError_t launch_mlp_bwd(const Scene &sc, const Mlp &m, Workspace &ws, float *g
         hipLaunchKernelGGL(k_mlp_bwd<false>, dim3((unsigned)(nwaves / 4)), dim3(BLOCK), 0, st, ws.Lp.as<float>(),
                            ws.Gp.as<float>(), m.w2a.as<float>(), m.w2b.as<float>(), m.tab.as<float4>(), W3,
                            ws.vorder.as<uint32_t>(), ws.items.as<int4>(), ws.n_items, items2, count2,
-                           std::max(nsub, 1), ws.Kp, sc.K, ws.live.as<uint8_t>(), ranked ? lw + LIST_AT : nullptr,
+                           nsub, ws.Kp, sc.K, ws.live.as<uint8_t>(), ranked ? lw + LIST_AT : nullptr,
                            ranked ? lw + BLOCK : nullptr, ws.dS.as<float2>(), ws.dL.as<float>(),
                            ws.dG.as<float>(), ws.mpart.as<float>(), DetMlp{});
     }
