@@ -581,13 +581,15 @@ __global__ __launch_bounds__(BLOCK) void k_rad_direct_bwd(const float2 *__restri
                                                           const uint32_t *__restrict__ order,
                                                           const unsigned long long *__restrict__ counters,
                                                           const int *__restrict__ rxview, int N, int64_t Kp,
-                                                          int64_t K, float *__restrict__ grad)
+                                                          int64_t K, const uint8_t *__restrict__ touch,
+                                                          float *__restrict__ grad)
 {
     const int64_t idx = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (idx >= (int64_t)N * Kp) return;
     const int64_t j = idx / Kp, s = idx - j * Kp;
     const int v = rxview[j];
     if (s >= (int64_t)counters[2 * (size_t)v]) return;
+    if (touch && !touch[((size_t)v * Kp + s) / MLP_PAIRS]) return;   // not cleared: nothing was added
     const float2 d = dS[idx];
     if (d.x == 0.f && d.y == 0.f) return;
     const int64_t k = min((int64_t)order[(size_t)v * Kp + s], K - 1);
@@ -1262,30 +1264,54 @@ __global__ __launch_bounds__(BLOCK) void k_proj_terms(const float *__restrict__ 
     pt[k] = p;
 }
 
+// A workgroup's blocks of 32 positions [b0, b0 + nb) (nb <= 256) that are marked in
+// `touch` (all of them without it), as a list in LDS; returns its length.
+__device__ __forceinline__ int touched_blocks(const uint8_t *__restrict__ touch, int64_t b0, int nb, uint32_t *s_list,
+                                              uint32_t *s_w)
+{
+    const int t = threadIdx.x;
+    const bool on = t < nb && (!touch || touch[b0 + t] != 0);
+    uint32_t tot;
+    const uint32_t at = block_exclusive_scan(on ? 1u : 0u, tot, s_w);
+    if (on) s_list[at] = (uint32_t)t;
+    __syncthreads();
+    return (int)tot;
+}
+
 // per (view, visible Gaussian); float atomics add the views' terms: mean
 // gradients to their output, Gs and glo per Gaussian (pacc, PACC_STRIDE
-// floats each) for k_project_fin
+// floats each) for k_project_fin.  A workgroup takes nb blocks of 32 positions,
+// a half wave each marked one: with marks 32 blocks (128 views of 1M 1,085 us
+// over all visible positions, 95 over the marked ones; 32 views of 100k 35 and
+// 25; by 256 blocks the marked ones, the nearest of each view, gather in few
+// workgroups: 81 and 60, by 16: 176 and 22).
 __global__ __launch_bounds__(BLOCK) void k_project_bwd(
     const ProjTerm *__restrict__ pt, int64_t K, int64_t Kp, const float *__restrict__ centres, int V, DevGrid g,
     const uint32_t *__restrict__ order, const unsigned long long *__restrict__ counters,
-    const float *__restrict__ g2d, float *__restrict__ gmeans, float *__restrict__ pacc)
+    const uint8_t *__restrict__ touch, int nb, const float *__restrict__ g2d, float *__restrict__ gmeans,
+    float *__restrict__ pacc)
 {
-    const int64_t p = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (p >= (int64_t)V * Kp) return;
-    const int64_t v = p / Kp, s = p - v * Kp;
-    if (s >= (int64_t)counters[2 * (size_t)v]) return;
-    const float *gg = g2d + (size_t)p * 8;
-    if (g2d_zero(gg)) return;
-    const int64_t k = min((int64_t)order[p], K - 1);
-    const ProjTerm q = pt[k];
-    const double S[3][3] = {{q.S[0], q.S[1], q.S[2]}, {q.S[1], q.S[3], q.S[4]}, {q.S[2], q.S[4], q.S[5]}};
-    const ViewGrad r = view_grad(q.pos.x, q.pos.y, q.pos.z, S, centres, v, g, gg);
-    if (gmeans)
-        for (int a = 0; a < 3; a++) atomicAdd(&gmeans[3 * k + a], (float)r.gp[a]);
-    if (pacc) {
-        float *acc = pacc + (size_t)k * PACC_STRIDE;
-        for (int a = 0; a < 6; a++) atomicAdd(&acc[a], (float)r.Gs[a]);
-        atomicAdd(&acc[6], (float)r.glo);
+    __shared__ uint32_t s_list[BLOCK];
+    __shared__ uint32_t s_w[4];
+    const int64_t b0 = (int64_t)blockIdx.x * nb;
+    const int n = touched_blocks(touch, b0, (int)min((int64_t)nb, (int64_t)V * Kp / MLP_PAIRS - b0), s_list, s_w);
+    for (int i = threadIdx.x / MLP_PAIRS; i < n; i += BLOCK / MLP_PAIRS) {
+        const int64_t p = (b0 + s_list[i]) * MLP_PAIRS + (threadIdx.x & (MLP_PAIRS - 1));
+        const int64_t v = p / Kp, s = p - v * Kp;
+        if (s >= (int64_t)counters[2 * (size_t)v]) continue;
+        const float *gg = g2d + (size_t)p * 8;
+        if (g2d_zero(gg)) continue;
+        const int64_t k = min((int64_t)order[p], K - 1);
+        const ProjTerm q = pt[k];
+        const double S[3][3] = {{q.S[0], q.S[1], q.S[2]}, {q.S[1], q.S[3], q.S[4]}, {q.S[2], q.S[4], q.S[5]}};
+        const ViewGrad r = view_grad(q.pos.x, q.pos.y, q.pos.z, S, centres, v, g, gg);
+        if (gmeans)
+            for (int a = 0; a < 3; a++) atomicAdd(&gmeans[3 * k + a], (float)r.gp[a]);
+        if (pacc) {
+            float *acc = pacc + (size_t)k * PACC_STRIDE;
+            for (int a = 0; a < 6; a++) atomicAdd(&acc[a], (float)r.Gs[a]);
+            atomicAdd(&acc[6], (float)r.glo);
+        }
     }
 }
 
@@ -1571,29 +1597,68 @@ __global__ __launch_bounds__(BLOCK) void k_zero_ranges(ZeroRanges z)
     for (size_t i = (size_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (size_t)gridDim.x * BLOCK) p[i] = 0u;
 }
 
-// zeroes, per segment y (a view, or a receiver and its view), the words of
-// the view's visible positions only: [0, visible(view) x wpr) of the
-// segment's Kp x wpr words (nothing reads the rest)
-__global__ __launch_bounds__(BLOCK) void k_zero_visible(uint32_t *__restrict__ p, int64_t Kp, int wpr,
-                                                        const unsigned long long *__restrict__ counters,
-                                                        const int *__restrict__ segview, int nseg)
+// Marks the blocks of 32 positions the blend backward may add to: those of a
+// tile's entries up to the last one any of its pixels composited (the forward's
+// stop indices).  Grid (tile, forward chunk); one pixel per thread, and only
+// the chunk that owns the view's stop indices works.
+__global__ __launch_bounds__(BLOCK) void k_mark_touched(const uint32_t *__restrict__ pval,
+                                                        const uint2 *__restrict__ ranges, const int *__restrict__ nlast,
+                                                        const int4 *__restrict__ chunks, int64_t Kp, DevGrid g,
+                                                        uint8_t *__restrict__ touch)
 {
-    const int y = blockIdx.y;
-    if (y >= nseg) return;
-    const int v = segview ? segview[y] : y;
-    const size_t n = (size_t)min((int64_t)counters[2 * (size_t)v], Kp) * (size_t)wpr;
-    uint32_t *base = p + (size_t)y * (size_t)Kp * (size_t)wpr;
-    for (size_t i = (size_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (size_t)gridDim.x * BLOCK) base[i] = 0u;
+    static_assert(TILE * TILE == BLOCK, "one pixel per thread");
+    __shared__ int s_max[4];
+    const int4 ch = chunks[blockIdx.y];
+    if (ch.w < 0) return;
+    const int view = ch.x, tile = blockIdx.x, t = threadIdx.x;
+    const int ty = tile / g.tiles_x, tx = tile - ty * g.tiles_x;
+    const int row = ty * TILE + t / TILE, col = tx * TILE + t % TILE;
+    int m = row < g.H && col < g.W ? nlast[((size_t)ch.w * g.H + row) * g.W + col] : 0;
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+    if ((t & 63) == 0) s_max[t >> 6] = m;
+    __syncthreads();
+    m = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+    const uint2 rg = ranges[(size_t)view * g.tiles + tile];
+    m = min(m, (int)(rg.y - rg.x));
+    const int64_t view_end = ((int64_t)view + 1) * Kp;
+    for (int i = t; i < m; i += BLOCK)
+        touch[min((int64_t)pval[rg.x + i], view_end - 1) / MLP_PAIRS] = 1;
 }
 
-hipError_t launch_zero_visible(uint32_t *p, int64_t Kp, int wpr, const unsigned long long *counters,
-                               const int *segview, int nseg, hipStream_t st)
+// Clears what the backward accumulates per position, in the marked blocks only:
+// the record gradients and dL/ds of every row of the view.  Nothing reads the
+// rest.  A workgroup takes 256 blocks, a half wave each marked one.  128 views of
+// 1M: all visible positions took 655 us, the marks and these 40.
+__global__ __launch_bounds__(BLOCK) void k_zero_touched(const uint8_t *__restrict__ touch, int64_t nblocks, int64_t Kp,
+                                                        const int4 *__restrict__ vinfo, float4 *__restrict__ g2d,
+                                                        float2 *__restrict__ dS)
 {
-    if (nseg <= 0 || Kp <= 0) return hipSuccess;
-    if (nseg > 65535) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)std::min<size_t>(nblk((size_t)Kp * (size_t)wpr), 1024);
-    hipLaunchKernelGGL(k_zero_visible, dim3(blocks, (unsigned)nseg), dim3(BLOCK), 0, st, p, Kp, wpr, counters,
-                       segview, nseg);
+    __shared__ uint32_t s_list[BLOCK];
+    __shared__ uint32_t s_w[4];
+    const int64_t b0 = (int64_t)blockIdx.x * BLOCK;
+    const int n = touched_blocks(touch, b0, (int)min((int64_t)BLOCK, nblocks - b0), s_list, s_w);
+    const int l = threadIdx.x & (MLP_PAIRS - 1);
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = threadIdx.x / MLP_PAIRS; i < n; i += BLOCK / MLP_PAIRS) {
+        const int64_t p = (b0 + s_list[i]) * MLP_PAIRS, v = p / Kp, s = p - v * Kp;
+        g2d[2 * p + l] = z;
+        g2d[2 * p + MLP_PAIRS + l] = z;
+        const int4 vi = vinfo[v];   // first row, rows
+        for (int j = vi.x; j < vi.x + vi.y; j++) dS[(int64_t)j * Kp + s + l] = make_float2(0.f, 0.f);
+    }
+}
+
+// Marks, then clears (the marks themselves are cleared beforehand).
+hipError_t launch_zero_touched(Workspace &ws, hipStream_t st)
+{
+    if (ws.n_chunks == 0 || ws.V == 0 || ws.Kp == 0) return hipSuccess;
+    if (ws.n_chunks > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mark_touched, dim3((unsigned)ws.g.tiles, (unsigned)ws.n_chunks), dim3(BLOCK), 0, st,
+                       ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(), ws.nlast.as<int>(), ws.d_chunks, ws.Kp,
+                       ws.g, ws.touch.as<uint8_t>());
+    const int64_t nblocks = (int64_t)ws.V * ws.Kp / MLP_PAIRS;
+    hipLaunchKernelGGL(k_zero_touched, dim3(nblk((size_t)nblocks)), dim3(BLOCK), 0, st, ws.touch.as<uint8_t>(), nblocks,
+                       ws.Kp, ws.d_vinfo, ws.g2d.as<float4>(), ws.dS.as<float2>());
     return hipGetLastError();
 }
 
@@ -1736,7 +1801,7 @@ hipError_t launch_rad_bwd(const Scene &sc, Workspace &ws, float *grad, hipStream
     if (n == 0 || !grad || sc.K == 0) return hipSuccess;
     hipLaunchKernelGGL(k_rad_direct_bwd, dim3(nblk(n)), dim3(BLOCK), 0, st, ws.dS.as<float2>(),
                        ws.vorder.as<uint32_t>(), ws.counters.as<unsigned long long>(),
-                       ws.d_rxview, ws.N, ws.Kp, sc.K, grad);
+                       ws.d_rxview, ws.N, ws.Kp, sc.K, ws.touched ? ws.touch.as<uint8_t>() : nullptr, grad);
     return hipGetLastError();
 }
 
@@ -1849,8 +1914,10 @@ hipError_t launch_project_bwd(const Scene &sc, Workspace &ws, const rxgs_grads &
     const bool cov = gr.log_scales || gr.quats || gr.logits;
     hipLaunchKernelGGL(k_proj_terms, dim3(nblk(sc.K)), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,
                        ws.pterm.as<ProjTerm>());
-    hipLaunchKernelGGL(k_project_bwd, dim3(nblk(n)), dim3(BLOCK), 0, st, ws.pterm.as<ProjTerm>(), sc.K, ws.Kp,
-                       ws.centres_p, ws.V, ws.g, ws.vorder.as<uint32_t>(), ws.counters.as<unsigned long long>(),
+    const int nb = ws.touched ? 32 : BLOCK / MLP_PAIRS;   // few marked blocks: more per workgroup
+    hipLaunchKernelGGL(k_project_bwd, dim3((unsigned)((n / MLP_PAIRS + nb - 1) / nb)), dim3(BLOCK), 0, st,
+                       ws.pterm.as<ProjTerm>(), sc.K, ws.Kp, ws.centres_p, ws.V, ws.g, ws.vorder.as<uint32_t>(),
+                       ws.counters.as<unsigned long long>(), ws.touched ? ws.touch.as<uint8_t>() : nullptr, nb,
                        ws.g2d.as<float>(), gr.means, cov ? ws.pacc.as<float>() : nullptr);
     if (cov)
         hipLaunchKernelGGL(k_project_fin, dim3(nblk(sc.K)), dim3(BLOCK), 0, st, sc.soa.as<float>(), sc.K,

@@ -320,14 +320,16 @@ bool ensure_pinned(Workspace &ws, size_t bytes)
     return true;
 }
 
-// Size (bytes of the 2-D record gradients) above which the backward clears
-// its per-position accumulators at visible positions only (256 MiB);
-// RXGS_ZERO_VISIBLE_MIN overrides it (0: always), so that tests can take
-// that path on small scenes.
+// Size (bytes of the 2-D record gradients) above which the backward marks the
+// blocks of composited entries and clears and reads its per-position accumulators
+// only there (48 MiB: 1.5M positions; the marks cost two launches, about 12 us,
+// and save clearing and reading 40 and 32 bytes per position at some 4 TB/s).
+// RXGS_ZERO_VISIBLE_MIN overrides it (0: always), so that tests can take that
+// path on small scenes.
 size_t zero_visible_min()
 {
     const char *e = std::getenv("RXGS_ZERO_VISIBLE_MIN");
-    return (e && e[0]) ? (size_t)std::strtoull(e, nullptr, 10) : ((size_t)256 << 20);
+    return (e && e[0]) ? (size_t)std::strtoull(e, nullptr, 10) : ((size_t)48 << 20);
 }
 
 // every device buffer of a workspace released (carved ones only forgotten)
@@ -342,7 +344,7 @@ void release_buffers(Workspace &ws)
                       &ws.dG,      &ws.mpart,   &ws.w1part,  &ws.mred,   &ws.live,   &ws.items_live, &ws.vflag,
                       &ws.items_far, &ws.frec, &ws.fcnt,  &ws.ftile,  &ws.hist_b, &ws.gfeat_tmp, &ws.gmlp_tmp,
                       &ws.rgam,    &ws.rab,     &ws.rloc,    &ws.gP,     &ws.dSP,
-                      &ws.oinv,    &ws.rank,    &ws.lcnt,    &ws.dLv,     &ws.dGp,    &ws.bins,
+                      &ws.oinv,    &ws.rank,    &ws.lcnt,    &ws.dLv,     &ws.dGp,    &ws.bins,    &ws.touch,
                       &ws.pterm,   &ws.pacc};
     for (DevBuf *b : bufs) release(*b);
 }
@@ -1778,17 +1780,18 @@ extern "C" rxgs_status rxgs_render_backward(rxgs_ctx *ctx, const rxgs_saved *sav
         return RXGS_OK;
     }
     const size_t VK = (size_t)ws.V * ws.Kp;
+    ws.touched = false;
     if (ws.det) return backward_det(ctx, ws, C, dC, dP, dA, gr, zr, st);
     WGROW(ctx, ws, ws.dS, (size_t)ws.N * ws.Kp * 8);
     WGROW(ctx, ws, ws.g2d, VK * 32);
     WGROW(ctx, ws, ws.live, VK / MLP_PAIRS + 4);
-    // dL/ds and the 2-D record gradients are written and read at visible
-    // positions only; when they are large, only those are cleared
-    const bool rows = VK * 32 > zero_visible_min() && ws.N <= 65535 && ws.V <= 65535;
-    if (rows) {
-        const unsigned long long *cnt = ws.counters.as<unsigned long long>();
-        HIPCHK(ctx, launch_zero_visible(ws.dS.as<uint32_t>(), ws.Kp, 2, cnt, ws.d_rxview, ws.N, st));
-        HIPCHK(ctx, launch_zero_visible(ws.g2d.as<uint32_t>(), ws.Kp, 8, cnt, nullptr, ws.V, st));
+    // dL/ds and the 2-D record gradients are added to at composited entries
+    // only; when they are large, the blocks of those are marked, and only they
+    // are cleared and read
+    ws.touched = VK * 32 > zero_visible_min() && ws.n_chunks <= 65535;
+    if (ws.touched) {
+        WGROW(ctx, ws, ws.touch, VK / MLP_PAIRS + 4);
+        zr.add(ws.touch.p, (VK / MLP_PAIRS + 3) / 4);
     } else {
         zr.add(ws.dS.p, (size_t)ws.N * ws.Kp * 2);
         zr.add(ws.g2d.p, VK * 8);
@@ -1820,6 +1823,7 @@ extern "C" rxgs_status rxgs_render_backward(rxgs_ctx *ctx, const rxgs_saved *sav
         }
     }
     HIPCHK(ctx, launch_zero_ranges(zr, st));
+    if (ws.touched) HIPCHK(ctx, launch_zero_touched(ws, st));
     STAGE(ctx, "blend_bwd", launch_blend_bwd(ws, C, dC, dP, dA, st));
     if (ws.use_mlp)
         STAGE(ctx, "mlp_bwd", launch_mlp_bwd(sc, ctx->mlp, ws, gfeat, gmlp, st));

@@ -250,6 +250,8 @@ struct Workspace {
     DevBuf nvis_d;    // V int
     // backward scratch
     DevBuf dS;        // N x Kp float2
+    DevBuf touch;     // per block of 32 positions: the backward may add to it (touched: marked for this backward)
+    bool touched = false;
     DevBuf g2d;       // V x Kp x 8 (u, v, a, b, c, o partials)
     DevBuf dL;        // K x 64
     DevBuf dG;        // N x 64
@@ -371,10 +373,9 @@ struct ZeroRanges {
     }
 };
 hipError_t launch_zero_ranges(const ZeroRanges &z, hipStream_t st);
-// zeroes the visible positions' words of per-view (segview NULL) or
-// per-receiver (segview: receiver -> view) rows of Kp x wpr words (backward.hip)
-hipError_t launch_zero_visible(uint32_t *p, int64_t Kp, int wpr, const unsigned long long *counters,
-                               const int *segview, int nseg, hipStream_t st);
+// marks the blocks of 32 positions that hold composited entries and zeroes their
+// per-position accumulators (backward.hip)
+hipError_t launch_zero_touched(Workspace &ws, hipStream_t st);
 // sort.hip: stable segmented radix sort of (key, value) pairs by the low
 // `bits` key bits; segments of seg_len keys (a multiple of 4096), or given per
 // 4096-key unit by segtab; wsb holds sort_ws_bytes(n, bits, nseg) bytes and
