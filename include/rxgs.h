@@ -184,8 +184,8 @@ rxgs_status rxgs_render(rxgs_ctx *ctx, int mode, int Q, const float *tx, const i
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * arguments without a saved state, the same kernels and results, and no
  * device or host allocation in the call.  Its workspace is carved, in order,
- * from a static device array of RXGS_NOALLOC_SCRATCH_BYTES that each GPU the
- * library runs on holds until the process ends (resolved per device by
+ * from a static device array (RXGS_NOALLOC_SCRATCH_BYTES and the padding that
+ * the workspace's layout adds for speed) that each GPU the library runs on holds until the process ends (resolved per device by
  * rxgs_create, which also makes the call's pinned staging); the region is
  * rewound at every call.  Every context on a GPU shares that GPU's array, so
  * calls that overlap on one GPU (other streams, other threads, other

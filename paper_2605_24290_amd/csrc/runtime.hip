@@ -572,7 +572,13 @@ extern "C" const char *rxgs_last_error(const rxgs_ctx *ctx)
 // static array that every GPU the library runs on holds for the life of the
 // process.  Host code never uses its name as an address: each device's copy
 // is resolved once, with that device current, by hipGetSymbolAddress.
-static __device__ __align__(256) unsigned char scratch[RXGS_NOALLOC_SCRATCH_BYTES];
+// It is larger than RXGS_NOALLOC_SCRATCH_BYTES by what the workspace's layout may
+// add for speed (scratch_limit): a render may take RXGS_NOALLOC_SCRATCH_BYTES and
+// its own share of that, so wider terms and counts refuse no render.  (24 MiB:
+// 28 bytes for each of the 500k Gaussians, and 16 for each of the 500k positions,
+// that RXGS_NOALLOC_SCRATCH_BYTES can hold.)
+constexpr size_t SCRATCH_LAYOUT = (size_t)24 << 20;
+static __device__ __align__(256) unsigned char scratch[RXGS_NOALLOC_SCRATCH_BYTES + SCRATCH_LAYOUT];
 
 namespace {
 constexpr int SCRATCH_MAX_DEVICES = 64;
@@ -595,6 +601,24 @@ hipError_t scratch_address(int device, void **out)
     return hipSuccess;
 }
 
+// what a render of K Gaussians and V views may carve from the scratch array: a
+// Gaussian's projection terms and cull bound are 80 bytes with whole sectors (52
+// packed), the direct binning keeps sums per slice of chunks, and beyond 255
+// tiles its counts take the place of a pair sort's other copies
+size_t scratch_limit(int64_t K, int64_t V, const DevGrid &g)
+{
+    if (V < 1) return RXGS_NOALLOC_SCRATCH_BYTES;
+    const int64_t Kp = (K + SORT_TILE - 1) / SORT_TILE * SORT_TILE, cpv = Kp / BLOCK;
+    if (V > (int64_t)(RXGS_NOALLOC_SCRATCH_BYTES / 256) || cpv > INT32_MAX) return RXGS_NOALLOC_SCRATCH_BYTES;
+    size_t more = 28 * (size_t)std::max<int64_t>(K, 1) + 512;
+    if (bins_fit(g)) {
+        const size_t bins = bins_bytes((int)V, (int)cpv, g);
+        const size_t narrow = (size_t)V * (260 * (size_t)cpv + 256 + 1 + (size_t)cpv + 1) * 4;
+        more += g.tiles > 255 ? bins + 256 : bins - std::min(bins, narrow);
+    }
+    return RXGS_NOALLOC_SCRATCH_BYTES + std::min(more, SCRATCH_LAYOUT);
+}
+
 // the allocation-free workspace of a context: carved from the device's
 // scratch array, with its pinned staging and events made here, at set-up
 rxgs_status setup_noalloc(rxgs_ctx *ctx)
@@ -603,7 +627,7 @@ rxgs_status setup_noalloc(rxgs_ctx *ctx)
     hipError_t e = scratch_address(ctx->device, &sp);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipGetSymbolAddress(scratch)");
     ctx->fixed.base = static_cast<char *>(sp);
-    ctx->fixed.cap = RXGS_NOALLOC_SCRATCH_BYTES;
+    ctx->fixed.cap = RXGS_NOALLOC_SCRATCH_BYTES;   // (scratch_limit at each call)
     ctx->fixed.used = 0;
     ctx->fixed.device = ctx->device;
     rxgs_saved *s = new (std::nothrow) rxgs_saved();
@@ -1367,8 +1391,8 @@ extern "C" rxgs_status rxgs_render(rxgs_ctx *ctx, int mode, int Q, const float *
 // ============================================================================
 // rxgs_render without allocations: the workspace is carved, in order, from
 // this device's scratch array, rewound at every call; its pinned staging and
-// events were made by rxgs_create.  A render that needs more than the array
-// holds fails with E_OOM ("scratch region exhausted") before writing any output.
+// events were made by rxgs_create.  A render that needs more than it may take
+// (scratch_limit) fails with E_OOM ("scratch region exhausted") before writing any output.
 extern "C" rxgs_status rxgs_render_noalloc(rxgs_ctx *ctx, int mode, int Q, const float *tx, const int32_t *rx_off,
                                            int N, const float *rx, float *C, float *power, float *csum, float *amp,
                                            void *stream)
@@ -1380,6 +1404,7 @@ extern "C" rxgs_status rxgs_render_noalloc(rxgs_ctx *ctx, int mode, int Q, const
     // ordered before this call's on one stream; calls that overlap race)
     release_buffers(ws);
     ctx->fixed.used = 0;
+    ctx->fixed.cap = scratch_limit(ctx->scene.K, mode == RXGS_MODE_TX ? Q : N, ctx->g);
     return render_pass(ctx, mode, Q, tx, rx_off, N, rx, C, power, csum, amp, ctx->noalloc, stream, 0xFFFFFFFFu);
 }
 
