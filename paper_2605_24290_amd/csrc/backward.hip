@@ -274,7 +274,11 @@ __global__ __launch_bounds__(BLOCK) void k_blend_bwd(
 // LDS into the A layout of v_mfma_f32_16x16x4_f32; B's columns are the six
 // basis values and the 2 RC components of G, constants of the lane (16
 // registers).  The gradients of (u, v, a, b, c, log2 o) follow from the
-// moments per entry: du = X + u0, dv = Y + v0.  Before, every entry summed
+// moments per entry: du = X + u0, dv = Y + v0.  The contraction runs in four
+// chains, `a` in up to four, and D keeps what its additions round away: with
+// single serial sums the gradients of a 1,024-Gaussian step of 4 receivers were
+// 1.2 times as far from 64 bits as with tree sums over the wave, so they are
+// level (1.4e-7 of the norm, mean over the outputs and 24 draws).  Before, every entry summed
 // 6 + 2 R values over the wave by DPP and LDS atomics, each under its own
 // branch, about 60 instructions; now about 43 in all are left per entry, and the
 // kernel waits on LDS and the vector ALU alike (0.43 of the cycles each).  32
@@ -305,12 +309,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(RC <= 4 ?
     __shared__ float s_c[4][8][3];      // and its three wrap corrections
     __shared__ int s_max[4];
 
-    // grid: (rank of the tile in its view's longest-first order, chunk and
-    // block of RC of its rows); the tiles of a view together: their entries'
-    // records and gradients stay in the caches (views first: 326 against 247 us)
-    const int4 ch = chunks[blockIdx.y / split];
-    const int sub = blockIdx.y - (blockIdx.y / split) * split;
-    const int tile = torder ? (int)torder[(size_t)ch.x * g.tiles + blockIdx.x] : (int)blockIdx.x;
+    // grid: (rank of the tile in its view's longest-first order and block of RC of
+    // the chunk's rows, chunk); the tiles of a view together: their entries'
+    // records and gradients stay in the caches (views first: 326 against 247 us).
+    // The blocks of one tile together, as they read the same list (step of one
+    // view with 32 receivers 771 -> 757 us)
+    const int4 ch = chunks[blockIdx.y];
+    const int trank = blockIdx.x / split, sub = blockIdx.x - trank * split;
+    const int tile = torder ? (int)torder[(size_t)ch.x * g.tiles + trank] : trank;
     const int view = ch.x, j0 = ch.y + sub * RC, nrx = min(ch.z - sub * RC, RC);
     if (nrx <= 0) return;   // uniform over the block, before any barrier
     const int tread = tx_mode ? view : j0;
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(RC <= 4 ?
         G[r] = make_float2(0.f, 0.f);
         if (inside && r < nrx) G[r] = pixel_grad(C, dC, dP, dA, (size_t)(j0 + r), P, pix);
     }
-    float D = 0.f;
+    float D = 0.f, Dl = 0.f;   // the sum and what its additions rounded away
     int m = last;
     for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
     const int wlast = __builtin_amdgcn_readfirstlane(m);
@@ -492,19 +498,30 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(RC <= 4 ?
                     const float wc = fminf(W_MAX, wr);
                     const bool act = ih + k < n && e[k] < lim && wc >= ALPHA_MIN;
                     const float w = act ? wc : 0.f;
-                    float a = 0.f;
+                    // (chains of at most two receivers, added pairwise: fewer roundings)
+                    constexpr int NA = RC < 4 ? RC : 4;
+                    float ar[NA];
 #pragma unroll
-                    for (int r = 0; r < RC; r++) a = fmaf(G[r].x, sr[k][r].x, fmaf(G[r].y, sr[k][r].y, a));
-                    a = act ? a : 0.f;   // (a position no pixel composites may have no radiance)
+                    for (int r = 0; r < RC; r++) {
+                        const float ay = r < NA ? G[r].y * sr[k][r].y : fmaf(G[r].y, sr[k][r].y, ar[r % NA]);
+                        ar[r % NA] = fmaf(G[r].x, sr[k][r].x, ay);
+                    }
+#pragma unroll
+                    for (int o = 1; o < NA; o *= 2)
+#pragma unroll
+                        for (int r = 0; r + o < NA; r += 2 * o) ar[r] += ar[r + o];
+                    const float a = act ? ar[0] : 0.f;   // (a position no pixel composites may have no radiance)
                     // 1 / (1 - w) by the hardware reciprocal (1 ulp; 1 - w >= 0.01):
                     // over a pixel's few dozen composited entries the recovered
                     // transmittance stays within ~1e-6 of the forward's
                     const float rw = __builtin_amdgcn_rcpf(1.f - w);
                     const float Tb = T * rw;   // (w = 0: rw = 1)
                     const float tw = Tb * w;
-                    const float dw = fmaf(T, a, -D) * rw;
+                    const float dw = (fmaf(T, a, -D) - Dl) * rw;
                     const float gex = wr < W_MAX ? dw * w * LN2F : 0.f;
-                    D = fmaf(tw, a, D);
+                    const float Dn = fmaf(tw, a, D);
+                    Dl += fmaf(tw, a, D - Dn);
+                    D = Dn;
                     T = Tb;
                     sv[(4 * half + k) * BWD_LD + lane] = gex;
                     sv[(8 + 4 * half + k) * BWD_LD + lane] = tw;
@@ -534,18 +551,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(RC <= 4 ?
             for (int q = 0; q < 4; q++)
                 A[q] = *reinterpret_cast<const float4 *>(sv + bc * BWD_LD + 16 * bg + 4 * q);
             wave_lds_fence();
-            floatx4 acc[NCB];
+            // (four chains of 16 pixels, added pairwise: one of 64 rounds as often
+            // as a serial sum)
+            floatx4 part[NCB][4];
 #pragma unroll
-            for (int b = 0; b < NCB; b++) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 4; i++)
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const float Aq[4] = {A[q].x, A[q].y, A[q].z, A[q].w};
-#pragma unroll
-                for (int i = 0; i < 4; i++)
+                for (int q = 0; q < 4; q++) {
+                    const float Aq[4] = {A[q].x, A[q].y, A[q].z, A[q].w};
 #pragma unroll
                     for (int b = 0; b < NCB; b++)
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aq[i], B[b][4 * q + i], acc[b], 0, 0, 0);
-            }
+                        part[b][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            Aq[i], B[b][4 * q + i], i ? part[b][q] : floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                }
+            floatx4 acc[NCB];
+#pragma unroll
+            for (int b = 0; b < NCB; b++) acc[b] = (part[b][0] + part[b][1]) + (part[b][2] + part[b][3]);
             write_out(acc, i0);
         }
         __syncthreads();
@@ -1704,9 +1725,9 @@ static hipError_t blend_bwd_mm_launch(Workspace &ws, const float *C, const float
 {
     // forward chunks hold at most ws.R rows; split them into blocks of RC
     const int split = (ws.R + RC - 1) / RC;
-    const int64_t ny = (int64_t)ws.n_chunks * split;
-    if (ny > 65535 || ws.g.tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_blend_bwd_mm<RC>, dim3((unsigned)ws.g.tiles, (unsigned)ny), dim3(BLOCK), 0, st,
+    const int64_t nx = (int64_t)ws.g.tiles * split;
+    if ((int64_t)ws.n_chunks * split > 65535 || nx > 0x7fffffff) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_blend_bwd_mm<RC>, dim3((unsigned)nx, (unsigned)ws.n_chunks), dim3(BLOCK), 0, st,
                        ws.srec.as<float4>(), ws.pval[ws.pairs_buf].as<uint32_t>(), ws.ranges.as<uint2>(),
                        ws.rad.as<float2>(), ws.d_chunks, split, ws.Kp, ws.g, ws.mode == RXGS_MODE_TX ? 1 : 0, C, dC, dP, dA,
                        ws.Tfin.as<float>(), ws.nlast.as<int>(), ws.dS.as<float>(), ws.g2d.as<float>(),
