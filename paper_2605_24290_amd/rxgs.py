@@ -338,11 +338,13 @@ class Renderer:
     def release_idle_states(self) -> int:
         """Free the autograd function's kept forward states; returns how many there were."""
         n = 0
-        while self._idle:
-            h, _ = self._idle.pop()
+        while True:
+            try:
+                h, _ = self._idle.pop()   # (another thread may take the last one)
+            except IndexError:
+                return n
             lib().rxgs_saved_destroy(h)
             n += 1
-        return n
 
     def _roomy(self, call):
         """call(), and once more without the kept states if memory runs out."""
